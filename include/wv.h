@@ -319,6 +319,9 @@ int wv_gather_symbols(const wv_config* cfg, const int16_t* d_q, int nplanes, int
  * centring of uint8 input; 0 for planes analysed as centred floats).
  *   d_q or d_y (float packed subbands, used when d_q is NULL);
  *   d_xhat : float [nplanes][H][W];  d_u8 : optional uint8 clamp(rint(x_hat)).
+ * 32-channel, three-layer float filters have two arithmetics of the same accuracy,
+ * whose results differ in the last bits: with d_u8 the FP32 matrix units, without
+ * it split 16-bit operands (faster; infinite y saturates the filters).
  */
 int wv_synthesize(const wv_model* m, const int16_t* d_q, const float* d_y, int nplanes,
                   int H, int W, float delta_L, float delta_H, float offset, void* d_scratch,

@@ -403,6 +403,121 @@ VecRef pack_vec_last(PackBuf& pb, const float* blob, const ConvShape& s) {
     return r;
 }
 
+// A 1 -> 32 -> 32 -> 1 lifting filter as split 16-bit operands (LiftSplit).  The weights of
+// layers 1 and 2 and their biases are multiplied by 2 log2 e (the tanh kernels take exp2 of
+// the sum); layer 2's and 3's weights by a power of two that brings the largest into
+// [2^14, 2^15), so that both FP16 parts of every weight that matters are normal numbers.
+struct SplitRef {
+    size_t w1, w2, w3, b1, b2, b3;
+    float s2, s3;
+    bool ok;   // weights finite and small enough that no product overflows
+};
+
+static uint16_t host_f2h(double v) {   // |v| < 65504; FP16, round to nearest even
+    const uint16_t sign = std::signbit(v) ? 0x8000 : 0;
+    const double a = std::fabs(v);
+    if (a < std::ldexp(1.0, -14)) return sign | (uint16_t)std::nearbyint(std::ldexp(a, 24));   // 1024: smallest normal
+    int e;
+    std::frexp(a, &e);                                                 // a in [2^(e-1), 2^e)
+    const double mant = std::nearbyint(std::ldexp(a, 11 - e));         // [1024, 2048]
+    return sign | (uint16_t)(((e + 14) << 10) + ((int)mant - 1024));   // 2048 carries into the exponent
+}
+static double host_h2d(uint16_t h) {
+    const int e = (h >> 10) & 31, f = h & 1023;
+    const double a = e ? std::ldexp(1024.0 + f, e - 25) : std::ldexp((double)f, -24);
+    return h & 0x8000 ? -a : a;
+}
+static double host_bf2d(uint16_t b) {
+    const uint32_t u = (uint32_t)b << 16;
+    float f;
+    memcpy(&f, &u, 4);
+    return f;
+}
+
+SplitRef pack_lift_split(PackBuf& pb, const float* blob, const ConvShape& c1, const ConvShape& c2,
+                         const ConvShape& c3) {
+    SplitRef r{};
+    const double A = 2.0 / std::log(2.0);   // 2 log2 e
+    constexpr int SA = 10;                  // activations are scaled by 2^SA
+    r.w1 = pb.add(5 * 64 * 4);
+    r.w2 = pb.add(2 * 9 * 2 * 64 * 4);
+    r.w3 = pb.add(2 * 64 * 4);
+    r.b1 = pb.add(32);
+    r.b2 = pb.add(32);
+    r.b3 = pb.add(4);
+    r.ok = true;
+    double m2 = 0.0, m3 = 0.0;
+    auto scan = [&](size_t off, int n, double* mx) {
+        for (int i = 0; i < n; ++i) {
+            const double a = std::fabs((double)blob[off + i]);
+            if (!(a <= 16777216.0)) r.ok = false;   // also NaN
+            if (mx && a > *mx) *mx = a;
+        }
+    };
+    scan(c1.w_off, 9 * 32, nullptr);
+    scan(c1.b_off, 32, nullptr);
+    scan(c2.w_off, 9 * 32 * 32, &m2);
+    scan(c2.b_off, 32, nullptr);
+    scan(c3.w_off, 9 * 32, &m3);
+    scan(c3.b_off, 1, nullptr);
+    if (!r.ok) return r;
+    auto scale_exp = [](double mx) {   // k with mx 2^k in [2^14, 2^15), at most 60
+        if (mx == 0.0) return 0;
+        int e;
+        std::frexp(mx, &e);
+        return std::min(15 - e, 60);
+    };
+    const int k2 = scale_exp(m2 * A), k3 = scale_exp(m3);
+    r.s2 = (float)std::ldexp(1.0, -(SA + k2));
+    r.s3 = (float)std::ldexp(1.0, -(SA + k3));
+    // input channel of lane half hf, element j of K chunk c
+    auto chan = [](int c, int hf, int j) { return 8 * (2 * c + (j >> 2)) + 4 * hf + (j & 3); };
+    uint16_t* p1 = reinterpret_cast<uint16_t*>(pb.data.data() + r.w1);
+    for (int q = 0; q < 5; ++q)
+        for (int lane = 0; lane < 64; ++lane) {
+            const int tap = 2 * q + (lane >> 5), ch = lane & 31;
+            uint16_t b[3] = {0, 0, 0};
+            double v = tap < 9 ? A * blob[c1.w_off + (size_t)ch * 9 + tap] : 0.0;
+            for (int i = 0; i < 3; ++i) {
+                b[i] = host_f2bf((float)v);
+                v -= host_bf2d(b[i]);
+            }
+            // against the z parts {z0, z0, z0, z1, z1, z2, z1, z2}
+            const int part[8] = {0, 1, 2, 0, 1, 0, 2, 1};
+            for (int j = 0; j < 8; ++j) p1[((size_t)q * 64 + lane) * 8 + j] = b[part[j]];
+        }
+    uint16_t* p2 = reinterpret_cast<uint16_t*>(pb.data.data() + r.w2);
+    constexpr size_t low2 = (size_t)9 * 2 * 64 * 8;   // the low parts follow the high parts
+    for (int tap = 0; tap < 9; ++tap)
+        for (int c = 0; c < 2; ++c)
+            for (int lane = 0; lane < 64; ++lane)
+                for (int j = 0; j < 8; ++j) {
+                    const double v = std::ldexp(
+                        A * blob[c2.w_off + ((size_t)(lane & 31) * 32 + chan(c, lane >> 5, j)) * 9 + tap], k2);
+                    const size_t at = ((size_t)(tap * 2 + c) * 64 + lane) * 8 + j;
+                    p2[at] = host_f2h(v);
+                    p2[at + low2] = host_f2h(v - host_h2d(p2[at]));
+                }
+    // Rows 4 dx + dy are the taps (dy, dx) of the high parts, rows 16 + 4 dx + dy of the low parts.
+    uint16_t* p3 = reinterpret_cast<uint16_t*>(pb.data.data() + r.w3);
+    for (int c = 0; c < 2; ++c)
+        for (int lane = 0; lane < 64; ++lane)
+            for (int j = 0; j < 8; ++j) {
+                const int row = lane & 15, dx = row >> 2, dy = row & 3;
+                double v = 0.0;
+                if (dx < 3 && dy < 3)
+                    v = std::ldexp((double)blob[c3.w_off + (size_t)chan(c, lane >> 5, j) * 9 + 3 * dy + dx], k3);
+                const uint16_t hi = host_f2h(v);
+                p3[((size_t)c * 64 + lane) * 8 + j] = (lane & 31) < 16 ? hi : host_f2h(v - host_h2d(hi));
+            }
+    for (int ch = 0; ch < 32; ++ch) {
+        pb.data[r.b1 + ch] = (float)(A * blob[c1.b_off + ch]);
+        pb.data[r.b2 + ch] = (float)(A * blob[c2.b_off + ch]);
+    }
+    pb.data[r.b3] = blob[c3.b_off];
+    return r;
+}
+
 struct BlockRefs {
     MfmaRef in, p1a, p1b, p2a, p2b, ra, rb, out;
     size_t dw_w, dw_b;   // depth-wise [9][C], [C]
@@ -411,6 +526,7 @@ struct BlockRefs {
 struct HostModel {
     VecRef lift_first[4], lift_last[4];
     std::vector<MfmaRef> lift_mid[4];
+    SplitRef lift_split[4];
     MfmaRef lstm;
     std::vector<MfmaRef> ctx[4][4];
     BlockRefs blk[4][4];
@@ -421,7 +537,12 @@ struct HostModel {
 static const int kArDy[12] = {-2, -2, -2, -2, -2, -1, -1, -1, -1, -1, 0, 0};
 static const int kArDx[12] = {-2, -1, 0, 1, 2, -2, -1, 0, 1, 2, -2, -1};
 
-// Context layers are packed for the precision's kernel; lifting is always FP32.
+// The filter shape and mode that the split-operand lifting kernel takes: the integer lifting
+// rounds the filter outputs and has to repeat the analysis bit for bit.
+static bool lift_splittable(const wv_config& c) { return c.lift_ch == 32 && c.lift_layers == 3 && !c.lift_int; }
+
+// Context layers are packed for the precision's kernel; lifting is always FP32, or split
+// operands of FP32 accuracy.
 HostModel pack_all(PackBuf& pb, const float* blob, const wv_config& c, int precision) {
     const Manifest mf = make_manifest(c);
     HostModel hm;
@@ -431,6 +552,7 @@ HostModel pack_all(PackBuf& pb, const float* blob, const wv_config& c, int preci
         for (size_t l = 1; l + 1 < v.size(); ++l)
             hm.lift_mid[f].push_back(pack_mfma(pb, blob, v[l], 0, false, 0));
         hm.lift_last[f] = pack_vec_last(pb, blob, v.back());
+        if (lift_splittable(c)) hm.lift_split[f] = pack_lift_split(pb, blob, v[0], v[1], v[2]);
     }
     auto ctxpack = precision == WV_BF16 ? pack_mfma16 : precision == WV_FP8 ? pack_mfma8 : pack_mfma;
     hm.lstm = ctxpack(pb, blob, mf.lstm, 1, true, c.ctx_ch);
@@ -494,6 +616,8 @@ struct wv_model {
     int precision;
     VecLayer lift_first[4], lift_last[4];
     std::vector<MfmaLayer> lift_mid[4];
+    LiftSplit lift_split[4];
+    bool split_ok;                       // lift_split is filled
     MfmaLayer lstm;                      // WV_FP32
     std::vector<MfmaLayer> ctx[4][4];
     MfmaLayer16 lstm16;                  // WV_BF16
@@ -581,7 +705,12 @@ extern "C" int wv_model_create(const wv_config* cfg, const float* d_weights, lon
     wv_model* m = new wv_model();
     m->cfg = *cfg;
     m->precision = precision;
+    m->split_ok = lift_splittable(*cfg);
     for (int f = 0; f < 4; ++f) {
+        const SplitRef& sp = hm.lift_split[f];
+        m->split_ok = m->split_ok && sp.ok;
+        m->lift_split[f] = LiftSplit{base + sp.w1, base + sp.w2, base + sp.w3, base + sp.b1, base + sp.b2, base + sp.b3,
+                                     sp.s2, sp.s3};
         m->lift_first[f] = vec(hm.lift_first[f]);
         m->lift_last[f] = vec(hm.lift_last[f]);
         for (auto& r : hm.lift_mid[f]) m->lift_mid[f].push_back(mfma(r));
@@ -736,6 +865,11 @@ enum { F_PROW = 0, F_UROW = 1, F_PCOL = 2, F_UCOL = 3 };
 inline View vw(float* p, long long ps, int rs, int cs) { return View{p, ps, rs, cs}; }
 inline CView cvw(const float* p, long long ps, int rs, int cs) { return CView{p, ps, rs, cs}; }
 
+// The split-operand filters for one synthesis: float results only.  Bytes stay those of the FP32
+// kernels, whose sums round differently (a rounding tie could fall the other way).
+// WV_LIFT_FORM names an FP32 form.
+bool use_split(const wv_model* m, const uint8_t* d_u8) { return m->split_ok && !d_u8 && !getenv("WV_LIFT_FORM"); }
+
 // out = A + sign * (predict ? z + N(z) : z/2 + N(z)) on an h x w array.
 int run_filter(const wv_model* m, int f, CView z, CView A, View out, int N, int h, int w,
                int predict, float sign, float* a1, float* a2, hipStream_t s) {
@@ -766,6 +900,20 @@ int run_filter(const wv_model* m, int f, CView z, CView A, View out, int N, int 
         oth = t;
     }
     HIPCHK(launch_lift_last(m->lift_last[f], cur, z, A, out, N, h, w, predict, sign, m->cfg.lift_int, s));
+    return WV_OK;
+}
+
+// run_filter on one or two independent sets of N planes; the split kernel takes both in a launch.
+int run_filters(const wv_model* m, bool split, int f, const LiftIO* io, int sets, int N, int h, int w, int predict,
+                float sign, float* a1, float* a2, hipStream_t s) {
+    if (split) {
+        HIPCHK(launch_lift_split(m->lift_split[f], io[0], io[sets - 1], sets, N, h, w, predict, sign, s));
+        return WV_OK;
+    }
+    for (int k = 0; k < sets; ++k) {
+        const int rc = run_filter(m, f, io[k].z, io[k].A, io[k].out, N, h, w, predict, sign, a1, a2, s);
+        if (rc) return rc;
+    }
     return WV_OK;
 }
 
@@ -886,6 +1034,7 @@ static int synth_impl(const wv_model* m, const int16_t* d_q, const float* d_y, i
     float* lb = base + sc.lbuf;
     float* hb = base + sc.hbuf;
     const int J = m->cfg.levels;
+    const bool split = use_split(m, d_u8);
     const float* X = y + lay[0].off;
     long long xps = HW;
     for (int j = J; j >= 1; --j) {
@@ -894,29 +1043,26 @@ static int synth_impl(const wv_model* m, const int16_t* d_q, const float* d_y, i
         const Sub& sLH = lay[2 + 3 * (J - j)];
         const Sub& sHH = lay[3 + 3 * (J - j)];
         const long long bps = (long long)(2 * hs) * ws;
-        // inverse column step on (LL, LH) -> l: even = LL - U_col(LH); odd = LH + P_col(even)
-        rc = run_filter(m, F_UCOL, cvw(y + sLH.off, HW, ws, 1), cvw(X, xps, ws, 1),
-                        vw(lb, bps, 2 * ws, 1), N, hs, ws, 0, -1.f, a1, a2, s);
+        // inverse column step on (LL, LH) -> l and on (HL, HH) -> h:
+        // even = LL - U_col(LH); odd = LH + P_col(even)
+        const CView lh = cvw(y + sLH.off, HW, ws, 1), hh = cvw(y + sHH.off, HW, ws, 1);
+        const LiftIO even[2] = {{lh, cvw(X, xps, ws, 1), vw(lb, bps, 2 * ws, 1)},
+                                {hh, cvw(y + sHL.off, HW, ws, 1), vw(hb, bps, 2 * ws, 1)}};
+        rc = run_filters(m, split, F_UCOL, even, 2, N, hs, ws, 0, -1.f, a1, a2, s);
         if (rc) return rc;
-        rc = run_filter(m, F_PCOL, cvw(lb, bps, 2 * ws, 1), cvw(y + sLH.off, HW, ws, 1),
-                        vw(lb + ws, bps, 2 * ws, 1), N, hs, ws, 1, 1.f, a1, a2, s);
-        if (rc) return rc;
-        // inverse column step on (HL, HH) -> h
-        rc = run_filter(m, F_UCOL, cvw(y + sHH.off, HW, ws, 1), cvw(y + sHL.off, HW, ws, 1),
-                        vw(hb, bps, 2 * ws, 1), N, hs, ws, 0, -1.f, a1, a2, s);
-        if (rc) return rc;
-        rc = run_filter(m, F_PCOL, cvw(hb, bps, 2 * ws, 1), cvw(y + sHH.off, HW, ws, 1),
-                        vw(hb + ws, bps, 2 * ws, 1), N, hs, ws, 1, 1.f, a1, a2, s);
+        const LiftIO odd[2] = {{cvw(lb, bps, 2 * ws, 1), lh, vw(lb + ws, bps, 2 * ws, 1)},
+                               {cvw(hb, bps, 2 * ws, 1), hh, vw(hb + ws, bps, 2 * ws, 1)}};
+        rc = run_filters(m, split, F_PCOL, odd, 2, N, hs, ws, 1, 1.f, a1, a2, s);
         if (rc) return rc;
         // inverse row step: even = l - U_row(h); odd = h + P_row(even)
         const int ho = 2 * hs, wo = 2 * ws;
         float* xo = (j == 1) ? d_xhat : base + ((j & 1) ? sc.Xa : sc.Xb);
         const long long ops = (long long)ho * wo;
-        rc = run_filter(m, F_UROW, cvw(hb, bps, ws, 1), cvw(lb, bps, ws, 1), vw(xo, ops, wo, 2), N, ho,
-                        ws, 0, -1.f, a1, a2, s);
+        const LiftIO re = {cvw(hb, bps, ws, 1), cvw(lb, bps, ws, 1), vw(xo, ops, wo, 2)};
+        rc = run_filters(m, split, F_UROW, &re, 1, N, ho, ws, 0, -1.f, a1, a2, s);
         if (rc) return rc;
-        rc = run_filter(m, F_PROW, cvw(xo, ops, wo, 2), cvw(hb, bps, ws, 1), vw(xo + 1, ops, wo, 2), N,
-                        ho, ws, 1, 1.f, a1, a2, s);
+        const LiftIO ro = {cvw(xo, ops, wo, 2), cvw(hb, bps, ws, 1), vw(xo + 1, ops, wo, 2)};
+        rc = run_filters(m, split, F_PROW, &ro, 1, N, ho, ws, 1, 1.f, a1, a2, s);
         if (rc) return rc;
         X = xo;
         xps = ops;

@@ -69,6 +69,23 @@ struct VecLayer {
     int ch;
 };
 
+// A 1 -> 32 -> 32 -> 1 lifting filter with its weights split into 16-bit parts (see
+// pack_lift_split and wv_lift_split.hip); the tanh arguments are scaled by 2 log2 e.
+struct LiftSplit {
+    const void* w1;    // [5 tap pairs][64 lanes][8 bf16]
+    const void* w2;    // [high, low][9 taps][2 K chunks][64 lanes][8 fp16]
+    const void* w3;    // [2 K chunks][64 lanes][8 fp16]: rows are taps, high and low parts
+    const float* b1;   // [32]
+    const float* b2;   // [32]
+    const float* b3;   // [1]
+    float s2, s3;      // sums of layers 2 and 3 times these powers of two are the values
+};
+// What one filter application reads (z, A) and writes.
+struct LiftIO {
+    CView z, A;
+    View out;
+};
+
 struct ConvArgs {
     const float* in;       // NHWC float input [N][h >> in_up][w >> in_up][cin], or null (zeros)
     long long in_ps;       // plane stride (floats)
@@ -242,6 +259,10 @@ hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLa
 hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, CView z, CView A,
                              View out, int N, int h, int w, int predict, float sign, int lift_int,
                              hipStream_t s);
+// The same filter application with the convs on split 16-bit operands (wv_lift_split.hip), for one or
+// two sets of N planes of one size.
+hipError_t launch_lift_split(const LiftSplit& L, const LiftIO& io0, const LiftIO& io1, int sets, int N, int h, int w,
+                             int predict, float sign, hipStream_t s);
 // Zero `bytes` bytes at p (16-byte aligned) with a kernel.
 hipError_t launch_zero(void* p, size_t bytes, hipStream_t s);
 hipError_t launch_center_u8(const uint8_t* x8, float* xf, long long n, hipStream_t s);
