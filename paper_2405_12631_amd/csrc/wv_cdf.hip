@@ -12,11 +12,15 @@
 //     (F_j = F_max - ceil(F_max * (1 - C_j)), at least one count below F_max),
 //     so no digits are lost to 1 - tiny rounding to 1;
 //   * a running maximum makes the row non-decreasing.
-// A workgroup builds 64 rows in LDS, one thread per row, or (launches too small to
-// fill the GPU, where one thread's 128 serial entries set the time) LPR lanes per
-// row, each a contiguous slice of the entries, the running maximum completed by a
-// prefix maximum over the row's lanes; either way the 64 rows are then written out
-// as one contiguous, coalesced block, and the tables are the same.
+// What bounds it: outside the rows' windows only the writes (260 bytes a row), inside them the
+// tails, about 50 vector instructions per component and entry.  Windows differ: for scales spread
+// over a decade their mean is 25 entries, but the longest of 64 rows has 101.  So a workgroup
+// deals all the window entries of its rows evenly to its threads (a prefix sum of the window
+// lengths, a binary search per entry), stores F in LDS, and then writes row after row, a wave to
+// a row.  (One thread or four lanes per row, as before, step through the longest window of a
+// wave: 2.4 M such rows 1239 us, 1152 rows 27 us; now 452 us and 9 us, most of them the call.)  The running maximum is
+// the identity up to rounding, so a wave looks for a decrease in its row and only then takes the
+// prefix maximum.
 #include "wv_device.h"
 #include "wv_internal.h"
 
@@ -25,73 +29,113 @@
 namespace wv {
 namespace {
 
-constexpr int ROWS = 64;
+constexpr int NT = 256;     // threads
 constexpr int MAXE = 256;   // max entries per row (N_s + 1)
 
-template <int K, int DIST, int LPR>
-__global__ __launch_bounds__(ROWS * LPR) void cdf_k(const float* __restrict__ params, long long n, int smin,
-                                                   int nsym, uint16_t* __restrict__ out) {
-    extern __shared__ __attribute__((aligned(16))) uint16_t rows[];   // [ROWS][nsym + 1]
-    const int t = threadIdx.x / LPR;   // row of this lane in the block
-    const int sl = threadIdx.x % LPR;  // its slice of the row's entries
+// Inclusive prefix maximum over the wave's lanes.
+__device__ __forceinline__ int wave_prefix_max(int v, int lane) {
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const int o = __shfl_up(v, d);
+        if (lane >= d) v = max(v, o);
+    }
+    return v;
+}
+
+template <int K, int DIST, int ROWS>
+__global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, long long n, int smin, int nsym,
+                                           uint16_t* __restrict__ out) {
+    extern __shared__ __attribute__((aligned(16))) uint16_t F[];   // [ROWS][nsym + 1]: F_j inside the windows
+    __shared__ CdfRow<K, DIST> R[ROWS];
+    __shared__ int win[ROWS][2];                 // evaluated entries j1 <= j < j2
+    __shared__ int first[ROWS + 1];              // of a row's entries among the workgroup's
+    __shared__ int top[ROWS];                    // running maximum before a row's last words
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int E = nsym + 1;
     const long long row0 = (long long)blockIdx.x * ROWS;
-    const long long row = row0 + t;
     const int nrows = (int)((n - row0) < ROWS ? (n - row0) : ROWS);
-    uint16_t* my = rows + t * E;
-    // entries j = 1 .. nsym - 1 in LPR contiguous slices
-    const int per = (nsym - 1 + LPR - 1) / LPR;
-    const int ja = 1 + sl * per;
-    const int jb = ja + per < nsym ? ja + per : nsym;
-    int F = 0;
-    if (row < n) {
-        CdfRow<K, DIST> R;
-        cdf_setup<K, DIST>(params + row * (3 * K), smin, nsym, R);
-        // The slice in three runs, each lane with its own bounds, so a wave steps through
-        // its longest window rather than the union of its rows' windows: F = 0 below the
-        // window, evaluated inside it (running maximum within the slice), F_max - 1 above.
-        const int j1 = min(max(R.jlo, ja), jb);
-        const int j2 = max(min(R.jhi + 1, jb), j1);
-        for (int j = ja; j < j1; ++j) my[j] = (uint16_t)(LPR > 1 ? 0 : j);
-        for (int j = j1; j < j2; ++j) {
-            const int Fj = cdf_F_in<K, DIST>(R, j);
-            F = Fj > F ? Fj : F;
-            my[j] = (uint16_t)(LPR > 1 ? F : j + F);
+    if (tid < 64) {
+        int len = 0;
+        if (tid < nrows) {
+            CdfRow<K, DIST> r;
+            cdf_setup<K, DIST>(params + (row0 + tid) * (3 * K), smin, nsym, r);
+            R[tid] = r;
+            const int j1 = min(max(r.jlo, 1), nsym);
+            const int j2 = max(min(r.jhi + 1, nsym), j1);
+            win[tid][0] = j1;
+            win[tid][1] = j2;
+            len = j2 - j1;
         }
-        if (j2 < jb) F = max(F, R.Fmax - 1);
-        for (int j = j2; j < jb; ++j) my[j] = (uint16_t)(LPR > 1 ? F : j + F);
-    }
-    if constexpr (LPR > 1) {
-        // Maximum of F over the slices before this one: inclusive max-scan over the row's
-        // lanes, shifted by one (F >= 0, so 0 is neutral).
-        int incl = F;
+        int sum = len;
 #pragma unroll
-        for (int d = 1; d < LPR; d <<= 1) {
-            const int o = __shfl_up(incl, d, LPR);
-            if (sl >= d) incl = o > incl ? o : incl;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(sum, d);
+            if (lane >= d) sum += o;
         }
-        int pre = __shfl_up(incl, 1, LPR);
-        if (sl == 0) pre = 0;
-        if (row < n)
-            for (int j = ja; j < jb; ++j) {
-                const int f = my[j];
-                my[j] = (uint16_t)(j + (f > pre ? f : pre));
-            }
-    }
-    if (row < n && sl == 0) {
-        my[0] = 0;
-        my[nsym] = 0;   // 2^16 mod 2^16
+        if (tid < ROWS) first[tid + 1] = sum;
+        if (tid == 0) first[0] = 0;
     }
     __syncthreads();
-    // Contiguous copy of this block's rows.
-    uint16_t* dst = out + row0 * E;
-    const long long nel = (long long)nrows * E;
-    if ((((uintptr_t)dst) & 15) == 0 && (nel & 7) == 0) {
-        const uint4* src4 = reinterpret_cast<const uint4*>(rows);
-        uint4* dst4 = reinterpret_cast<uint4*>(dst);
-        for (long long i = threadIdx.x; i < nel / 8; i += ROWS * LPR) dst4[i] = src4[i];
-    } else {
-        for (long long i = threadIdx.x; i < nel; i += ROWS * LPR) dst[i] = rows[i];
+    const int total = first[ROWS];
+    for (int e = tid; e < total; e += NT) {
+        int r = 0;
+#pragma unroll
+        for (int d = ROWS / 2; d >= 1; d >>= 1)   // last row with first[r] <= e
+            if (first[r + d] <= e) r += d;
+        const int j = win[r][0] + e - first[r];
+        const CdfRow<K, DIST> row = R[r];
+        F[r * E + j] = (uint16_t)max(cdf_F_in<K, DIST>(row, j), 0);
+    }
+    __syncthreads();
+    const int Fmax = 65536 - nsym;
+    const bool words = (E & 1) == 0 && ((uintptr_t)out & 3) == 0;   // rows are whole 32-bit words
+    // F_j of a row, 0 at both ends of the table
+    auto value = [&](int r, int j, int j1, int j2) {
+        int f = j < j1 ? 0 : Fmax - 1;
+        if (j >= j1 && j < j2) f = F[r * E + j];
+        return f;
+    };
+    auto entry = [&](int j, int f) { return j == 0 || j >= nsym ? 0u : (uint32_t)(j + f) & 0xffffu; };
+    const int npairs = (E + 1) >> 1;
+    const int whole = npairs & ~63, rest = npairs - whole;
+    const bool tail = rest <= 4 && ROWS == 64;   // few pairs past a multiple of 64: lane = row for them
+    for (int r = wave; r < nrows; r += NT / 64) {
+        const int j1 = win[r][0], j2 = win[r][1];
+        uint16_t* o = out + (row0 + r) * E;
+        int run = 0;   // maximum of the entries so far
+        for (int base = 0; base < (tail ? whole : npairs); base += 64) {
+            const int j = 2 * (base + lane);
+            int f0 = value(r, j, j1, j2), f1 = value(r, j + 1, j1, j2);
+            const int before = lane ? __shfl_up(f1, 1) : run;
+            if (__ballot(f1 < f0 || f0 < (lane ? before : run))) {
+                int m = wave_prefix_max(max(f0, f1), lane);
+                const int ex = __shfl_up(m, 1);
+                f0 = max(f0, max(run, lane ? ex : 0));
+                f1 = max(f0, f1);
+            }
+            run = __shfl(f1, 63);
+            const uint32_t a = entry(j, f0), b = entry(j + 1, f1);
+            if (words) {
+                if (j < E) reinterpret_cast<uint32_t*>(o)[j >> 1] = a | (b << 16);
+            } else {
+                if (j < E) o[j] = (uint16_t)a;
+                if (j + 1 < E) o[j + 1] = (uint16_t)b;
+            }
+        }
+        if (tail && lane == 0) top[r] = run;
+    }
+    if (tail && rest > 0) {
+        __syncthreads();
+        for (int q = wave; q < rest; q += NT / 64) {
+            if (lane >= nrows) continue;
+            const int r = lane, j1 = win[r][0], j2 = win[r][1];
+            uint16_t* o = out + (row0 + r) * E;
+            int m = top[r];
+            for (int j = 2 * whole; j <= 2 * (whole + q) + 1 && j < E; ++j) {   // at most 8 entries
+                m = max(m, value(r, j, j1, j2));
+                if (j >= 2 * (whole + q)) o[j] = (uint16_t)entry(j, m);
+            }
+        }
     }
 }
 
@@ -101,18 +145,20 @@ hipError_t launch_cdf(const float* params, long long n, int K, int dist, int smi
                       uint16_t* cdf, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (nsym + 1 > MAXE || nsym < 2) return hipErrorInvalidValue;
-    const unsigned g = (unsigned)((n + ROWS - 1) / ROWS);
-    const size_t lds = ((size_t)ROWS * (nsym + 1) * sizeof(uint16_t) + 15) & ~(size_t)15;
-    // One lane per row once the launch has more than ~4 waves per SIMD of rows; below that
-    // the serial row length sets the time and 4 lanes per row take a quarter of it each.
-    const bool split = n <= 256ll * 1024;
-#define WV_CDF_CASE(KK, DD)                                                                                  \
-    if (K == KK && dist == DD) {                                                                             \
-        if (split)                                                                                           \
-            hipLaunchKernelGGL((cdf_k<KK, DD, 4>), dim3(g), dim3(ROWS * 4), lds, s, params, n, smin, nsym, cdf); \
-        else                                                                                                 \
-            hipLaunchKernelGGL((cdf_k<KK, DD, 1>), dim3(g), dim3(ROWS), lds, s, params, n, smin, nsym, cdf);     \
-        return hipGetLastError();                                                                            \
+    // 64 rows per workgroup share the fixed work best; up to about 100 000 rows (1500 such workgroups,
+    // under six per CU) 16 rows finish sooner: 16 000 rows 9 against 14 us, 74 000 rows 24.2 against
+    // 26.1 us, 150 000 rows 42.1 against 39.9 us.
+    const bool small = n <= 96 * 1024;
+    const int rows = small ? 16 : 64;
+    const unsigned g = (unsigned)((n + rows - 1) / rows);
+    const size_t lds = ((size_t)rows * (nsym + 1) * sizeof(uint16_t) + 15) & ~(size_t)15;
+#define WV_CDF_CASE(KK, DD)                                                                                     \
+    if (K == KK && dist == DD) {                                                                                \
+        if (small)                                                                                              \
+            hipLaunchKernelGGL((cdf_k<KK, DD, 16>), dim3(g), dim3(NT), lds, s, params, n, smin, nsym, cdf);        \
+        else                                                                                                    \
+            hipLaunchKernelGGL((cdf_k<KK, DD, 64>), dim3(g), dim3(NT), lds, s, params, n, smin, nsym, cdf);        \
+        return hipGetLastError();                                                                               \
     }
     WV_CDF_CASE(1, 0) WV_CDF_CASE(2, 0) WV_CDF_CASE(3, 0) WV_CDF_CASE(4, 0)
     WV_CDF_CASE(1, 1) WV_CDF_CASE(2, 1) WV_CDF_CASE(3, 1) WV_CDF_CASE(4, 1)
