@@ -15,12 +15,12 @@
 // What bounds it: outside the rows' windows only the writes (260 bytes a row), inside them the
 // tails, about 50 vector instructions per component and entry.  Windows differ: for scales spread
 // over a decade their mean is 25 entries, but the longest of 64 rows has 101.  So a workgroup
-// deals all the window entries of its rows evenly to its threads (a prefix sum of the window
-// lengths, a binary search per entry), stores F in LDS, and then writes row after row, a wave to
-// a row.  (One thread or four lanes per row, as before, step through the longest window of a
-// wave: 2.4 M such rows 1239 us, 1152 rows 27 us; now 452 us and 9 us, most of them the call.)  The running maximum is
-// the identity up to rounding, so a wave looks for a decrease in its row and only then takes the
-// prefix maximum.
+// fills its rows' entries outside the windows in LDS, deals all the window entries evenly to its
+// threads (a prefix sum of the window lengths, a binary search per entry), and copies the rows out
+// as one block.  (One thread or four lanes per row, as before, step through the longest window of a
+// wave: 2.4 M such rows 1239 us, 1152 rows 27 us; now 335 us and 5 us.  Rows as narrow as an
+// untrained model's, ten entries, run at the speed of the copy either way.)  The running maximum is the identity up to rounding, so entries are only compared with
+// their predecessors, and a row is gone through again if one of them is larger.
 #include "wv_device.h"
 #include "wv_internal.h"
 
@@ -32,38 +32,32 @@ namespace {
 constexpr int NT = 256;     // threads
 constexpr int MAXE = 256;   // max entries per row (N_s + 1)
 
-// Inclusive prefix maximum over the wave's lanes.
-__device__ __forceinline__ int wave_prefix_max(int v, int lane) {
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        const int o = __shfl_up(v, d);
-        if (lane >= d) v = max(v, o);
-    }
-    return v;
-}
-
 template <int K, int DIST, int ROWS>
 __global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, long long n, int smin, int nsym,
                                            uint16_t* __restrict__ out) {
-    extern __shared__ __attribute__((aligned(16))) uint16_t F[];   // [ROWS][nsym + 1]: F_j inside the windows
+    extern __shared__ __attribute__((aligned(16))) uint16_t tab[];   // [ROWS][nsym + 1]
     __shared__ CdfRow<K, DIST> R[ROWS];
-    __shared__ int win[ROWS][2];                 // evaluated entries j1 <= j < j2
-    __shared__ int first[ROWS + 1];              // of a row's entries among the workgroup's
-    __shared__ int top[ROWS];                    // running maximum before a row's last words
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    __shared__ int win[ROWS][2];        // evaluated entries j1 <= j < j2
+    __shared__ int first[ROWS + 1];     // of a row's entries among the workgroup's
+    __shared__ int bad[ROWS], anybad;   // rows whose F decreases somewhere
+    const int tid = threadIdx.x, lane = tid & 63;
     const int E = nsym + 1;
     const long long row0 = (long long)blockIdx.x * ROWS;
     const int nrows = (int)((n - row0) < ROWS ? (n - row0) : ROWS);
     if (tid < 64) {
         int len = 0;
-        if (tid < nrows) {
+        if (tid < ROWS) {
             CdfRow<K, DIST> r;
-            cdf_setup<K, DIST>(params + (row0 + tid) * (3 * K), smin, nsym, r);
-            R[tid] = r;
-            const int j1 = min(max(r.jlo, 1), nsym);
-            const int j2 = max(min(r.jhi + 1, nsym), j1);
+            int j1 = 1, j2 = 1;
+            if (tid < nrows) {
+                cdf_setup<K, DIST>(params + (row0 + tid) * (3 * K), smin, nsym, r);
+                R[tid] = r;
+                j1 = min(max(r.jlo, 1), nsym);
+                j2 = max(min(r.jhi + 1, nsym), j1);
+            }
             win[tid][0] = j1;
             win[tid][1] = j2;
+            bad[tid] = 0;
             len = j2 - j1;
         }
         int sum = len;
@@ -73,69 +67,69 @@ __global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, lo
             if (lane >= d) sum += o;
         }
         if (tid < ROWS) first[tid + 1] = sum;
-        if (tid == 0) first[0] = 0;
+        if (tid == 0) first[0] = anybad = 0;
+    }
+    __syncthreads();
+    const int Fmax = 65536 - nsym;
+    {   // cdf[j] = j below the window, j + F_max - 1 above it; the last entry 0 (a thread keeps its row)
+        const int r = tid % ROWS, j2 = win[r][1];
+        if ((E & 1) == 0) {
+            uint32_t* w = reinterpret_cast<uint32_t*>(tab + r * E);
+            for (int q = tid / ROWS; q < E / 2; q += NT / ROWS) {
+                const int j = 2 * q;
+                const uint32_t a = j + (j >= j2 ? Fmax - 1 : 0), b = j + 1 + (j + 1 >= j2 ? Fmax - 1 : 0);
+                w[q] = (a & 0xffffu) | (j + 1 == nsym ? 0u : b << 16);
+            }
+        } else {
+            for (int j = tid / ROWS; j < E; j += NT / ROWS)
+                tab[r * E + j] = j == nsym ? (uint16_t)0 : (uint16_t)(j + (j >= j2 ? Fmax - 1 : 0));
+        }
     }
     __syncthreads();
     const int total = first[ROWS];
-    for (int e = tid; e < total; e += NT) {
+    for (int e0 = tid - lane; e0 < total; e0 += NT) {
+        const int e = min(e0 + lane, total - 1);
         int r = 0;
 #pragma unroll
         for (int d = ROWS / 2; d >= 1; d >>= 1)   // last row with first[r] <= e
             if (first[r + d] <= e) r += d;
-        const int j = win[r][0] + e - first[r];
+        const int f = first[r], j1 = win[r][0], j = j1 + e - f;
         const CdfRow<K, DIST> row = R[r];
-        F[r * E + j] = (uint16_t)max(cdf_F_in<K, DIST>(row, j), 0);
+        const int F = max(cdf_F_in<K, DIST>(row, j), 0);
+        tab[r * E + j] = (uint16_t)(j + F);
+        // the row's entry before this one, except for the first lane (checked below)
+        const int before = __builtin_amdgcn_update_dpp(0, F, 0x138, 0xf, 0xf, false);   // wave_shr:1
+        if (lane > 0 && e > f && F < before) bad[r] = anybad = 1;
     }
     __syncthreads();
-    const int Fmax = 65536 - nsym;
-    const bool words = (E & 1) == 0 && ((uintptr_t)out & 3) == 0;   // rows are whole 32-bit words
-    // F_j of a row, 0 at both ends of the table
-    auto value = [&](int r, int j, int j1, int j2) {
-        int f = j < j1 ? 0 : Fmax - 1;
-        if (j >= j1 && j < j2) f = F[r * E + j];
-        return f;
-    };
-    auto entry = [&](int j, int f) { return j == 0 || j >= nsym ? 0u : (uint32_t)(j + f) & 0xffffu; };
-    const int npairs = (E + 1) >> 1;
-    const int whole = npairs & ~63, rest = npairs - whole;
-    const bool tail = rest <= 4 && ROWS == 64;   // few pairs past a multiple of 64: lane = row for them
-    for (int r = wave; r < nrows; r += NT / 64) {
-        const int j1 = win[r][0], j2 = win[r][1];
-        uint16_t* o = out + (row0 + r) * E;
-        int run = 0;   // maximum of the entries so far
-        for (int base = 0; base < (tail ? whole : npairs); base += 64) {
-            const int j = 2 * (base + lane);
-            int f0 = value(r, j, j1, j2), f1 = value(r, j + 1, j1, j2);
-            const int before = lane ? __shfl_up(f1, 1) : run;
-            if (__ballot(f1 < f0 || f0 < (lane ? before : run))) {
-                int m = wave_prefix_max(max(f0, f1), lane);
-                const int ex = __shfl_up(m, 1);
-                f0 = max(f0, max(run, lane ? ex : 0));
-                f1 = max(f0, f1);
-            }
-            run = __shfl(f1, 63);
-            const uint32_t a = entry(j, f0), b = entry(j + 1, f1);
-            if (words) {
-                if (j < E) reinterpret_cast<uint32_t*>(o)[j >> 1] = a | (b << 16);
-            } else {
-                if (j < E) o[j] = (uint16_t)a;
-                if (j + 1 < E) o[j + 1] = (uint16_t)b;
-            }
-        }
-        if (tail && lane == 0) top[r] = run;
+    for (int e = 64 * tid; e < total; e += 64 * NT) {   // entries that a first lane evaluated
+        int r = 0;
+#pragma unroll
+        for (int d = ROWS / 2; d >= 1; d >>= 1)
+            if (first[r + d] <= e) r += d;
+        const uint16_t* c = tab + r * E + win[r][0] + e - first[r];
+        if (e > first[r] && c[0] <= c[-1]) bad[r] = anybad = 1;
     }
-    if (tail && rest > 0) {
-        __syncthreads();
-        for (int q = wave; q < rest; q += NT / 64) {
-            if (lane >= nrows) continue;
-            const int r = lane, j1 = win[r][0], j2 = win[r][1];
-            uint16_t* o = out + (row0 + r) * E;
-            int m = top[r];
-            for (int j = 2 * whole; j <= 2 * (whole + q) + 1 && j < E; ++j) {   // at most 8 entries
-                m = max(m, value(r, j, j1, j2));
-                if (j >= 2 * (whole + q)) o[j] = (uint16_t)entry(j, m);
+    __syncthreads();
+    if (anybad) {
+        if (tid < ROWS && bad[tid]) {   // running maximum of F
+            int m = 0;
+            for (int j = win[tid][0]; j < nsym; ++j) {
+                m = max(m, (int)tab[tid * E + j] - j);
+                tab[tid * E + j] = (uint16_t)(j + m);
             }
         }
+        __syncthreads();
+    }
+    // Contiguous copy of this block's rows.
+    uint16_t* dst = out + row0 * E;
+    const int nel = nrows * E;
+    if ((((uintptr_t)dst) & 15) == 0 && (nel & 7) == 0) {
+        const uint4* src4 = reinterpret_cast<const uint4*>(tab);
+        uint4* dst4 = reinterpret_cast<uint4*>(dst);
+        for (int i = tid; i < nel / 8; i += NT) dst4[i] = src4[i];
+    } else {
+        for (int i = tid; i < nel; i += NT) dst[i] = tab[i];
     }
 }
 
@@ -146,8 +140,8 @@ hipError_t launch_cdf(const float* params, long long n, int K, int dist, int smi
     if (n == 0) return hipSuccess;
     if (nsym + 1 > MAXE || nsym < 2) return hipErrorInvalidValue;
     // 64 rows per workgroup share the fixed work best; up to about 100 000 rows (1500 such workgroups,
-    // under six per CU) 16 rows finish sooner: 16 000 rows 9 against 14 us, 74 000 rows 24.2 against
-    // 26.1 us, 150 000 rows 42.1 against 39.9 us.
+    // six per CU) 16 rows finish sooner: 1152 rows 5.1 against 9.4 us, 74 000 rows 18.0 against
+    // 18.8 us, 150 000 rows 30.4 against 28.8 us.
     const bool small = n <= 96 * 1024;
     const int rows = small ? 16 : 64;
     const unsigned g = (unsigned)((n + rows - 1) / rows);
