@@ -62,6 +62,24 @@ __device__ __forceinline__ void mixture_head(const float* v, int K, float sigma_
     }
 }
 
+// Component k of mixture_head: the same operations, so the same bits.
+template <class OutPtr>
+__device__ __forceinline__ void mixture_head_part(const float* v, int K, int k, float sigma_min, OutPtr o) {
+    float mx = v[0];
+    for (int i = 1; i < K; ++i) mx = fmaxf(mx, v[i]);
+    float se = 0.f, ek = 0.f;
+    for (int i = 0; i < K; ++i) {
+        const float e = __expf(v[i] - mx);
+        se += e;
+        ek = i == k ? e : ek;
+    }
+    o[k] = ek / se;
+    o[K + k] = v[K + k];
+    const float x = v[2 * K + k];
+    const float sp = log1pf(__expf(-fabsf(x))) + fmaxf(x, 0.f);
+    o[2 * K + k] = fmaxf(sp, sigma_min);
+}
+
 // One row of the 16-bit CDF table (see wv_cdf_tables): setup from the
 // parameters, then F_j before the running maximum.
 template <int K, int DIST>
