@@ -9,7 +9,8 @@
 // each of its 4 waves 4 rows x (16 NB) channels (16 accumulators for NB = 4).
 // A fragments: one 16-byte LDS read = 8 channels of one position per lane;
 // B fragments: per-tap weight slices staged in LDS in three buffers, read from
-// HBM/L2 two taps ahead and stored to LDS one tap ahead.  Activations in and out are BF16 (NHWC), the
+// HBM/L2 two taps ahead and stored to LDS one tap ahead; with few workgroups
+// (ALLW) all taps at once before the loop.  Activations in and out are BF16 (NHWC), the
 // LSTM cell state, every epilogue and the mixture parameters are FP32.
 //
 // FP8 form (F8): the same tiling, activations stored as e4m3 bytes, weights
@@ -82,30 +83,43 @@ __device__ __forceinline__ floatx4 mfma_lp(const typename Frag<F8>::T& a, const 
 }
 
 template <int CIN, int NB, bool SYM, int MODE, bool F8>
-__device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvArgs& a, const int tile_idx,
-                                               const int ycol) {
-    using FragT = typename Frag<F8>::T;
+struct Geo {
     // Two taps per K = 128 step (see above) for the 64-channel step-stack layers without the
     // symbol channel (with it, or the ConvLSTM's 256 gate columns, the larger operands leave
     // the persistent form too few registers).  The weight packer applies the same rule.
-    constexpr bool K128 = F8 && CIN == 64 && !SYM && MODE != CONV_LSTM;
-    constexpr int ES = F8 ? 1 : 2;              // bytes per activation element
-    constexpr int FB = 8 * ES;                  // bytes per operand fragment (8 K values)
+    static constexpr bool K128 = F8 && CIN == 64 && !SYM && MODE != CONV_LSTM;
+    static constexpr int ES = F8 ? 1 : 2;              // bytes per activation element
+    static constexpr int FB = 8 * ES;                  // bytes per operand fragment (8 K values)
     // bytes per halo position (conflict-free reads; 16-byte aligned for the 32-byte K128 reads)
-    constexpr int STRIDE = K128 ? CIN + 16 : CIN * ES + 8 * ES;
-    constexpr int CC = K128 ? 1 : CIN / 32;     // K chunks per staged B slice (a tap, or a K128 step)
-    constexpr int BU = K128 ? 128 : FB * 64 / 16;   // uint4 per (chunk, 16-column block) of B
-    constexpr int BV = CC * NB * BU;            // uint4 of B per tap (K128: per step) for this workgroup
-    constexpr int NSTEP = K128 ? 5 : 9;         // staged B slices: taps, or K128 steps
+    static constexpr int STRIDE = K128 ? CIN + 16 : CIN * ES + 8 * ES;
+    static constexpr int CC = K128 ? 1 : CIN / 32;     // K chunks per staged B slice (a tap, or a K128 step)
+    static constexpr int BU = K128 ? 128 : FB * 64 / 16;   // uint4 per (chunk, 16-column block) of B
+    static constexpr int BV = CC * NB * BU;            // uint4 of B per tap (K128: per step) for this workgroup
+    static constexpr int NSTEP = K128 ? 5 : 9;         // staged B slices: taps, or K128 steps
+    static constexpr int OS = NB * 16 * ES + 16;       // bytes per position of the staged output tile
+    // Input halo; after the MFMA loop it holds the output tile (RELU/TANH epilogue).
+    static constexpr int LDS_IN = HALO * STRIDE > TH * TW * OS ? HALO * STRIDE : TH * TW * OS;
+    // Whether two workgroups a CU fit with all of the weights in LDS.
+    static constexpr bool ALL_FITS = LDS_IN + NSTEP * BV * 16 + (SYM ? NB * 1024 + 2 * HALO : 0) +
+                                         (MODE == CONV_HEAD ? 8 * TW * 17 * 4 : 0) <= 80 * 1024;
+};
+
+template <int CIN, int NB, bool SYM, int MODE, bool F8, bool ALLW>
+__device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvArgs& a, const int tile_idx,
+                                               const int ycol) {
+    using FragT = typename Frag<F8>::T;
+    using G = Geo<CIN, NB, SYM, MODE, F8>;
+    constexpr bool K128 = G::K128;
+    constexpr int ES = G::ES, STRIDE = G::STRIDE, CC = G::CC, BU = G::BU, BV = G::BV, NSTEP = G::NSTEP, OS = G::OS,
+                  LDS_IN = G::LDS_IN;
     constexpr int BPT = (BV + 255) / 256;
+    constexpr int NBUF = ALLW ? NSTEP : 3;      // B slices in LDS
+    constexpr int NREG = ALLW ? NSTEP : 2;      // B slices in registers on their way there
     constexpr int NSY = (HALO + 255) / 256;     // symbol positions per thread
     constexpr int MB = (MODE == CONV_HEAD) ? 2 : 4;   // head: only the rows of its step's parity
-    constexpr int OS = NB * 16 * ES + 16;       // bytes per position of the staged output tile
     static_assert(BPT <= 2, "B slice too large");
-    // Input halo; after the MFMA loop it holds the output tile (RELU/TANH epilogue).
-    constexpr int LDS_IN = HALO * STRIDE > TH * TW * OS ? HALO * STRIDE : TH * TW * OS;
     __shared__ __attribute__((aligned(16))) uint8_t lds_in[LDS_IN];
-    __shared__ __attribute__((aligned(16))) uint4 lds_w[3][BV];
+    __shared__ __attribute__((aligned(16))) uint4 lds_w[NBUF][BV];
     __shared__ __attribute__((aligned(16))) uint4 lds_ws[SYM ? NB * 64 : 1];
     __shared__ uint16_t lds_s[SYM ? HALO : 1];
     __shared__ float lds_head[MODE == CONV_HEAD ? 8 * TW * 17 : 1];
@@ -135,20 +149,21 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     const long long bo1 = BPT > 1 ? boff_of(1) : 0;
     const long long btap = (long long)CC * L.nbt * BU;
     // B slice k (a tap, or a K128 step) goes global -> registers (set k % 2) two slices ahead,
-    // registers -> LDS buffer k % 3 one slice ahead.
-    uint4 bq[2][2];
+    // registers -> LDS buffer k % 3 one slice ahead; with ALLW all of them before the loop.
+    uint4 bq[NREG][2];
 #define WV_LOAD_B(tp)                                       \
     {                                                       \
         const uint4* wt_ = wg + (long long)(tp) * btap;     \
-        bq[(tp) & 1][0] = ld_g(wt_ + bo0);                  \
-        if (BPT > 1) bq[(tp) & 1][1] = ld_g(wt_ + bo1);     \
+        bq[(tp) % NREG][0] = ld_g(wt_ + bo0);                  \
+        if (BPT > 1) bq[(tp) % NREG][1] = ld_g(wt_ + bo1);     \
     }
 #define WV_STORE_B(tp)                                                                            \
     {                                                                                             \
-        if (BV >= 256 || tid < BV) lds_w[(tp) % 3][tid] = bq[(tp) & 1][0];                        \
-        if (BPT > 1 && (BV >= 512 || tid + 256 < BV)) lds_w[(tp) % 3][tid + 256] = bq[(tp) & 1][1]; \
+        if (BV >= 256 || tid < BV) lds_w[(tp) % NBUF][tid] = bq[(tp) % NREG][0];                        \
+        if (BPT > 1 && (BV >= 512 || tid + 256 < BV)) lds_w[(tp) % NBUF][tid + 256] = bq[(tp) % NREG][1]; \
     }
-    WV_LOAD_B(0)
+#pragma unroll
+    for (int k = 0; k < (ALLW ? NSTEP : 1); ++k) WV_LOAD_B(k)
 
     {
         const int win = a.w >> a.in_up;
@@ -220,8 +235,9 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
             store_halo();
         }
     }
-    WV_STORE_B(0)
-    WV_LOAD_B(1)
+#pragma unroll
+    for (int k = 0; k < (ALLW ? NSTEP : 1); ++k) WV_STORE_B(k)
+    if constexpr (!ALLW) WV_LOAD_B(1)
     __syncthreads();
 
     floatx4 acc[MB][NB];
@@ -229,6 +245,13 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    // Bias and (FP8) scale of packed column nc, needed after the loop.
+    float bia[NB], csc[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb) {
+        bia[nb] = gmem(L.bias)[(nblk0 + nb) * 16 + (lane & 15)];
+        csc[nb] = F8 ? gmem(L.scale)[(nblk0 + nb) * 16 + (lane & 15)] : 1.f;
+    }
 
     const int m = lane & 15;
     const int kk = lane >> 4;
@@ -244,11 +267,11 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     const intx8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
     for (int st = 0; st < NSTEP; ++st) {
-        if (st + 2 < NSTEP) {
+        if (!ALLW && st + 2 < NSTEP) {
             WV_LOAD_B(st + 2)
             __builtin_amdgcn_sched_barrier(0);   // keep the loads ahead of this step's MFMAs
         }
-        const uint8_t* wb = reinterpret_cast<const uint8_t*>(lds_w[st % 3]);
+        const uint8_t* wb = reinterpret_cast<const uint8_t*>(lds_w[st % NBUF]);
         intx8 bv[NB];
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) bv[nb] = load32(wb + (nb * BU + 2 * lane) * 16);
@@ -262,7 +285,7 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma_f8k128(av, bv[nb], acc[mb][nb]);
         }
-        if (st + 1 < NSTEP) {
+        if (!ALLW && st + 1 < NSTEP) {
             WV_STORE_B(st + 1)   // buffer (st + 1) % 3 was last read two steps ago
             __syncthreads();
         }
@@ -275,11 +298,11 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     WV_LOAD_A(afr[0], 0, 0)
 #pragma unroll
     for (int tap = 0; tap < 9; ++tap) {
-        if (tap < 7) {
+        if (!ALLW && tap < 7) {
             WV_LOAD_B(tap + 2)
             __builtin_amdgcn_sched_barrier(0);   // keep the loads ahead of this tap's MFMAs
         }
-        const FragT* wb = reinterpret_cast<const FragT*>(lds_w[tap % 3]);
+        const FragT* wb = reinterpret_cast<const FragT*>(lds_w[tap % NBUF]);
         FragT bv[CC][NB];
 #pragma unroll
         for (int cc = 0; cc < CC; ++cc)
@@ -298,7 +321,7 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
 #pragma unroll
                 for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = mfma_lp<F8>(afr[st & 1][mb], bv[cc][nb], acc[mb][nb]);
         }
-        if (tap < 8) {
+        if (!ALLW && tap < 8) {
             WV_STORE_B(tap + 1)   // buffer (tap + 1) % 3 was last read two taps ago
             __syncthreads();
         }
@@ -329,9 +352,6 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     const int col = lane & 15;
     const int rowq = (lane >> 4) * 4;
     // FP8: the accumulator of packed column nc is scaled by L.scale[nc] before the bias.
-    float csc[NB];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) csc[nb] = F8 ? gmem(L.scale)[(nblk0 + nb) * 16 + col] : 1.f;
     if constexpr (MODE == CONV_RELU || MODE == CONV_TANH) {
         // Stage the output tile [256 positions][16 NB channels] in LDS (reusing the
         // halo buffer), then write 16-byte chunks: full, coalesced lines.
@@ -341,7 +361,7 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
         for (int mb = 0; mb < MB; ++mb)
 #pragma unroll
             for (int nb = 0; nb < NB; ++nb) {
-                const float b = gmem(L.bias)[(nblk0 + nb) * 16 + col];
+                const float b = bia[nb];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     float v = F8 ? fmaf(acc[mb][nb][i], csc[nb], b) : acc[mb][nb][i] + b;
@@ -369,11 +389,7 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
         }
     } else if constexpr (MODE == CONV_LSTM) {
         const int ch = ycol * 16 + col;
-        const auto bias = gmem(L.bias);
-        const float bi = bias[(nblk0 + 0) * 16 + col];
-        const float bf = bias[(nblk0 + 1) * 16 + col];
-        const float bg = bias[(nblk0 + 2) * 16 + col];
-        const float bo = bias[(nblk0 + 3) * 16 + col];
+        const float bi = bia[0], bf = bia[1 % NB], bg = bia[2 % NB], bo = bia[3 % NB];
         const int wp = a.w >> a.cprev_up;
         // All of this lane's previous cell states first (one wait for all of them, not one per
         // position; c_prev and c_out are different buffers).
@@ -419,7 +435,7 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
 #pragma unroll
             for (int i = 0; i < 4; ++i)
                 lds_head[((wave * 2 + mb) * TW + rowq + i) * 17 + col] =
-                    F8 ? fmaf(acc[mb][0][i], csc[0], gmem(L.bias)[col]) : acc[mb][0][i] + gmem(L.bias)[col];
+                    F8 ? fmaf(acc[mb][0][i], csc[0], bia[0]) : acc[mb][0][i] + bia[0];
         __syncthreads();
         if (tid < 8 * TW) {
             const int rr = tid / TW;                       // 0..7: wave rr/2, block rr%2
@@ -439,14 +455,14 @@ __device__ __forceinline__ void conv_tile_bf16(const MfmaLayer16& L, const ConvA
     }
 }
 
-template <int CIN, int NB, bool SYM, int MODE, bool F8>
+template <int CIN, int NB, bool SYM, int MODE, bool F8, bool ALLW>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void conv3x3_mfma_bf16(
     const MfmaLayer16 L, const ConvArgs a) {
     long long tile;
     int ycol;
     conv_item_order(blockIdx.x, (long long)a.tiles_x * a.tiles_y * a.N, MODE == CONV_HEAD ? 1 : L.nbt / NB, tile,
                     ycol);
-    conv_tile_bf16<CIN, NB, SYM, MODE, F8>(L, a, (int)tile, ycol);
+    conv_tile_bf16<CIN, NB, SYM, MODE, F8, ALLW>(L, a, (int)tile, ycol);
 }
 
 // Persistent multi-segment form (see the FP32 kernel).
@@ -465,7 +481,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void c
         int ycol;
         conv_item_order(local, (long long)S.a.tiles_x * S.a.tiles_y * S.a.N, MODE == CONV_HEAD ? 1 : S.L.nbt / NB,
                         tile, ycol);
-        conv_tile_bf16<CIN, NB, SYM, MODE, F8>(S.L, S.a, (int)tile, ycol);
+        conv_tile_bf16<CIN, NB, SYM, MODE, F8, false>(S.L, S.a, (int)tile, ycol);
         __syncthreads();
     }
 }
@@ -477,7 +493,17 @@ hipError_t launch_t(const MfmaLayer16& L, const ConvArgs& a0, hipStream_t s) {
     a.tiles_y = (a.h + TH - 1) / TH;
     const int ncols = (MODE == CONV_HEAD) ? 1 : L.nbt / NB;
     dim3 grid((unsigned)(a.tiles_x * a.tiles_y * a.N * ncols));
-    hipLaunchKernelGGL((conv3x3_mfma_bf16<CIN, NB, SYM, MODE, F8>), grid, dim3(256), 0, s, L, a);
+    // All weights before the loop, where latency counts: a tap of one or two blocks computes for 60 to
+    // 250 cycles, so slices read two taps ahead are waited for at every tap.  Up to one workgroup a CU
+    // that costs nothing; up to two (2.3) rounds of one where two still fit a CU.  A 512 x 768 image's
+    // launches of 36 to 252 workgroups went from 7.6 to 7.0 us, the decode from 4.44 to 4.35 ms (FP8: 3.43
+    // to 3.35); beyond these lines the copy of 36 KB is exposed instead (all that fit: FP8 3.55 ms; up to
+    // 600 workgroups that do not fit twice: BF16 4.63).
+    constexpr bool FITS = Geo<CIN, NB, SYM, MODE, F8>::ALL_FITS;
+    if (grid.x <= 256 || (FITS && grid.x <= 600))
+        hipLaunchKernelGGL((conv3x3_mfma_bf16<CIN, NB, SYM, MODE, F8, true>), grid, dim3(256), 0, s, L, a);
+    else
+        hipLaunchKernelGGL((conv3x3_mfma_bf16<CIN, NB, SYM, MODE, F8, false>), grid, dim3(256), 0, s, L, a);
     return hipGetLastError();
 }
 
