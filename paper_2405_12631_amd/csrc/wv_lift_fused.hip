@@ -29,7 +29,7 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 
 template <int C, int OH, int OW, int NWV>
 __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, const MfmaLayer L2, const VecLayer L3,
-                                                        const CView z, const CView A, const View out, int N,
+                                                        const LiftIO io0, const LiftIO io1, int N,
                                                         int h, int w, int tiles_x, int tiles_y, int cbeg,
                                                         int predict, float sign, int lift_int, int total) {
     constexpr int NT = 64 * NWV;            // threads
@@ -67,7 +67,8 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
     constexpr int NZ = (ZH * ZW + NT - 1) / NT;
     float zv_next[NZ];
     auto load_z = [&](const Tile& T) {
-        const float* zp = z.p + (long long)T.n * z.ps;
+        const CView& z = T.n < N ? io0.z : io1.z;
+        const float* zp = z.p + (long long)(T.n < N ? T.n : T.n - N) * z.ps;
 #pragma unroll
         for (int k = 0; k < NZ; ++k) {
             const int i = tid + k * NT;
@@ -109,7 +110,9 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
 
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     const Tile T = tile_of(t);
-    const int n = T.n, r0 = T.r0, c0 = T.c0;
+    const int n = T.n < N ? T.n : T.n - N, r0 = T.r0, c0 = T.c0;
+    const CView& A = T.n < N ? io0.A : io1.A;
+    const View& out = T.n < N ? io0.out : io1.out;
     __syncthreads();   // the previous tile is done with zs and act (and the weights are in LDS)
 #pragma unroll
     for (int k = 0; k < NZ; ++k)
@@ -287,24 +290,27 @@ long long lift_resident() {   // resident workgroups, cached per device (256 if 
 }
 
 template <int C, int OH, int OW, int NWV>
-hipError_t lift_launch(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, CView z, CView A, View out, int N,
+hipError_t lift_launch(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets, int N,
                        int h, int w, int predict, float sign, int lift_int, hipStream_t s, int cbeg = 0) {
     const int tx = (w - cbeg + OW - 1) / OW, ty = (h + OH - 1) / OH;
-    const long long total = (long long)tx * ty * N;
+    const long long total = (long long)tx * ty * N * sets;
     if (total >= (1ll << 31)) return hipErrorInvalidValue;
     const long long res = lift_resident<C, OH, OW, NWV>();
     const long long g = total < res ? total : res;
-    hipLaunchKernelGGL((lift_fused_k<C, OH, OW, NWV>), dim3((unsigned)g), dim3(64 * NWV), 0, s, L1, L2, L3, z, A, out,
-                       N, h, w, tx, ty, cbeg, predict, sign, lift_int, (int)total);
+    hipLaunchKernelGGL((lift_fused_k<C, OH, OW, NWV>), dim3((unsigned)g), dim3(64 * NWV), 0, s, L1, L2, L3, io[0],
+                       io[sets - 1], N, h, w, tx, ty, cbeg, predict, sign, lift_int, (int)total);
     return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, CView z, CView A,
-                             View out, int N, int h, int w, int predict, float sign, int lift_int,
-                             hipStream_t s) {
+hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets,
+                             int N, int h, int w, int predict, float sign, int lift_int, hipStream_t s) {
     if ((long long)N * h * w == 0) return hipSuccess;
+    if (sets == 2 && (long long)N * h * w >= 1ll << 31) {   // the launches count tiles in 31 bits
+        const hipError_t e = launch_lift_fused(L1, L2, L3, io, 1, N, h, w, predict, sign, lift_int, s);
+        return e != hipSuccess ? e : launch_lift_fused(L1, L2, L3, io + 1, 1, N, h, w, predict, sign, lift_int, s);
+    }
     if (L1.ch == 32 && L2.cin == 32 && L2.nbt == 2) {
         // Wide arrays stream rows (wv_lift_rows.hip) in 124-column strips; a last strip that
         // would be less than 70 % used is left to the tiles as a band of the remaining columns
@@ -320,23 +326,23 @@ hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecL
         const bool partial = 10 * rem >= 7 * LIFT_ROWS_OUTW;   // the last strip in rows too
         const int nrows = full + (partial ? 1 : 0);              // strips in rows
         if (!force_tile && nrows > 0 &&
-            (force_rows || (long long)nrows * N * h >= LIFT_ROWS_MIN_STRIP_ROWS)) {
-            hipError_t e = launch_lift_rows(L1, L2, L3, z, A, out, N, h, w, nrows, predict, sign, lift_int, s);
+            (force_rows || (long long)nrows * N * sets * h >= LIFT_ROWS_MIN_STRIP_ROWS)) {
+            hipError_t e = launch_lift_rows(L1, L2, L3, io, sets, N, h, w, nrows, predict, sign, lift_int, s);
             if (e != hipSuccess || partial || rem == 0) return e;
-            return lift_launch<32, 8, 16, 4>(L1, L2, L3, z, A, out, N, h, w, predict, sign, lift_int, s,
+            return lift_launch<32, 8, 16, 4>(L1, L2, L3, io, sets, N, h, w, predict, sign, lift_int, s,
                                              full * LIFT_ROWS_OUTW);
         }
         // The 16 x 32 tile needs one 8-wave workgroup per CU, whose phases (vector layer 1, MFMA
         // layer 2, layer 3) no longer overlap with a second workgroup's; it pays off only where
         // its lower recompute has many rounds of tiles to work on (measured: 1088 x 1920 planes
         // 5.37 -> 4.63 ms per synthesis, 512 x 768 planes 1.26 -> 1.52 ms).
-        const long long big = (long long)((w + 31) / 32) * ((h + 15) / 16) * N;
+        const long long big = (long long)((w + 31) / 32) * ((h + 15) / 16) * N * sets;
         if (big >= 2048)
-            return lift_launch<32, 16, 32, 8>(L1, L2, L3, z, A, out, N, h, w, predict, sign, lift_int, s);
-        return lift_launch<32, 8, 16, 4>(L1, L2, L3, z, A, out, N, h, w, predict, sign, lift_int, s);
+            return lift_launch<32, 16, 32, 8>(L1, L2, L3, io, sets, N, h, w, predict, sign, lift_int, s);
+        return lift_launch<32, 8, 16, 4>(L1, L2, L3, io, sets, N, h, w, predict, sign, lift_int, s);
     }
     if (L1.ch == 16 && L2.cin == 16 && L2.nbt == 1)
-        return lift_launch<16, 8, 16, 4>(L1, L2, L3, z, A, out, N, h, w, predict, sign, lift_int, s);
+        return lift_launch<16, 8, 16, 4>(L1, L2, L3, io, sets, N, h, w, predict, sign, lift_int, s);
     return hipErrorInvalidValue;
 }
 

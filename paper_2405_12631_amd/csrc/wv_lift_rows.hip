@@ -156,7 +156,7 @@ __device__ __forceinline__ void mfma_role(const MfmaLayer& L2, int h, int w, int
 }
 
 // Layer 1, the middle layer's bias and tanh, layer 3 and the update; vector lane v of 0..255.
-__device__ __forceinline__ void vec_role(const VecLayer& L3, CView z, CView A, View out, int h, int w, int nstrips,
+__device__ __forceinline__ void vec_role(const VecLayer& L3, const LiftIO& io0, const LiftIO& io1, int N, int h, int w, int nstrips,
                                          int nseg, int seg_rows, int predict, float sign, int lift_int, long long total,
                                          int v, const Smem& S) {
     const float b3 = L3.bias[0];
@@ -170,9 +170,13 @@ __device__ __forceinline__ void vec_role(const VecLayer& L3, CView z, CView A, V
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const Item I = item_of(it, nstrips, nseg, seg_rows, h);
         const int T = I.R + 10;
-        const float* zp = z.p + (long long)I.n * z.ps;
-        const float* ap = A.p + (long long)I.n * A.ps;
-        float* op = out.p + (long long)I.n * out.ps;
+        const LiftIO& io = I.n < N ? io0 : io1;
+        const CView &z = io.z, &A = io.A;
+        const View& out = io.out;
+        const int n = I.n < N ? I.n : I.n - N;
+        const float* zp = z.p + (long long)n * z.ps;
+        const float* ap = A.p + (long long)n * A.ps;
+        float* op = out.p + (long long)n * out.ps;
         auto zload = [&](int r) {   // z row r at column c0 - 3 + v (lanes 0 .. ZN - 1)
             const int c = I.c0 - 3 + v;
             return (v < ZN && r >= 0 && r < h && c >= 0 && c < w) ? zp[(long long)r * z.rs + (long long)c * z.cs] : 0.f;
@@ -301,7 +305,7 @@ __device__ __forceinline__ void vec_role(const VecLayer& L3, CView z, CView A, V
 }
 
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void lift_rows_k(
-    const VecLayer L1, const MfmaLayer L2, const VecLayer L3, const CView z, const CView A, const View out, int h,
+    const VecLayer L1, const MfmaLayer L2, const VecLayer L3, const LiftIO io0, const LiftIO io1, int N, int h,
     int w, int nstrips, int nseg, int seg_rows, int predict, float sign, int lift_int, long long total) {
     __shared__ __attribute__((aligned(16))) uint8_t a1[R1][A1N * PB];
     __shared__ __attribute__((aligned(16))) uint8_t a2[R2][NPOS * PB];
@@ -325,7 +329,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
     if (wave < 4)
         mfma_role(L2, h, w, nstrips, nseg, seg_rows, total, wave, S);
     else
-        vec_role(L3, z, A, out, h, w, nstrips, nseg, seg_rows, predict, sign, lift_int, total, tid - 256, S);
+        vec_role(L3, io0, io1, N, h, w, nstrips, nseg, seg_rows, predict, sign, lift_int, total, tid - 256, S);
 }
 
 }  // namespace
@@ -333,7 +337,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(2))) void l
 // Rows per item: each item pays 10 row steps of pipeline fill, and a launch takes as many
 // rounds of the resident workgroups as its items need, so the number of row segments is the
 // one that minimises rounds x (rows per segment + 10).
-hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, CView z, CView A, View out,
+hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets,
                             int N, int h, int w, int nstrips, int predict, float sign, int lift_int, hipStream_t s) {
     if ((long long)N * h * w == 0 || nstrips == 0) return hipSuccess;
     if (nstrips < 0 || (long long)(nstrips - 1) * OUTW >= w) return hipErrorInvalidValue;
@@ -351,7 +355,7 @@ hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLa
         resident = per_cu * cus;
         cache[dev].store(resident, std::memory_order_relaxed);
     }
-    const long long cols = (long long)nstrips * N;
+    const long long cols = (long long)nstrips * N * sets;
     int seg_rows = h;
     long long best = -1;
     for (int ns = 1; ns <= h; ++ns) {
@@ -368,7 +372,7 @@ hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLa
     const int nseg = (h + seg_rows - 1) / seg_rows;
     const long long total = cols * nseg;
     const long long g = total < resident ? total : resident;
-    hipLaunchKernelGGL(lift_rows_k, dim3((unsigned)g), dim3(512), 0, s, L1, L2, L3, z, A, out, h, w, nstrips, nseg,
+    hipLaunchKernelGGL(lift_rows_k, dim3((unsigned)g), dim3(512), 0, s, L1, L2, L3, io[0], io[sets - 1], N, h, w, nstrips, nseg,
                        seg_rows, predict, sign, lift_int, total);
     return hipGetLastError();
 }
