@@ -52,13 +52,23 @@ enum {
 };
 
 /* Arithmetic of the context-model convolutions (ConvLSTM and step stacks; the
- * lifting transform, the mixture head's epilogue and the CDF tables are FP32 in
- * every mode).  WV_BF16: BF16 operands and activations, FP32 accumulation.
+ * lifting transform (but see WV_LIFT_SPLIT), the mixture head's epilogue and the
+ * CDF tables are FP32 in every mode).  WV_BF16: BF16 operands and activations, FP32 accumulation.
  * WV_FP8: e4m3 weights with one FP32 scale per output channel (scale = max |w|
  * of the channel / 448), e4m3 activations (unscaled, saturated at +-448),
  * FP32 accumulation, symbols fed through a BF16 chunk so they stay exact.
  * Reduced precision needs ctx_ch of 32 or 64 and ctx_arch 0. */
 typedef enum { WV_FP32 = 0, WV_BF16 = 1, WV_FP8 = 2 } wv_precision;
+
+/* Or-ed to the precision of wv_pack_bytes and wv_model_create: every synthesis
+ * of the model (floats, bytes and impulse responses alike) takes its filters on
+ * the 16-bit matrix units, each FP32 operand split into two or three 16-bit
+ * parts (22 to 24 bits).  About 2.5 times as fast as FP32 with the same error
+ * against 64 bits, but other last bits, and infinite subbands saturate the
+ * filters where FP32 sums may give NaN.  Needs lift_ch 32, lift_layers 3,
+ * lift_int 0 and filter weights of at most 2^24 (WV_EUNSUPPORTED otherwise).
+ * Analysis, and so symbols and streams, are those of the model without it. */
+enum { WV_LIFT_SPLIT = 256 };
 
 /* Component family of the per-coefficient mixture.  Sec. 3.1 uses a Laplacian
  * (mean and scale); the workload's default is a K-component Gaussian mixture. */
@@ -319,9 +329,6 @@ int wv_gather_symbols(const wv_config* cfg, const int16_t* d_q, int nplanes, int
  * centring of uint8 input; 0 for planes analysed as centred floats).
  *   d_q or d_y (float packed subbands, used when d_q is NULL);
  *   d_xhat : float [nplanes][H][W];  d_u8 : optional uint8 clamp(rint(x_hat)).
- * 32-channel, three-layer float filters have two arithmetics of the same accuracy,
- * whose results differ in the last bits: with d_u8 the FP32 matrix units, without
- * it split 16-bit operands (faster; infinite y saturates the filters).
  */
 int wv_synthesize(const wv_model* m, const int16_t* d_q, const float* d_y, int nplanes,
                   int H, int W, float delta_L, float delta_H, float offset, void* d_scratch,

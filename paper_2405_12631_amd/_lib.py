@@ -15,6 +15,7 @@ LIB_PATH = os.path.join(_HERE, "libwv.so")
 WV_OK, WV_EINVAL, WV_ESHAPE, WV_EORDER, WV_EDEVICE, WV_ECORRUPT, WV_EUNSUPPORTED, WV_ENOMEM = \
     0, -1, -2, -3, -4, -5, -6, -7
 WV_FP32, WV_BF16, WV_FP8 = 0, 1, 2
+WV_LIFT_SPLIT = 256
 WV_DIST_GAUSS, WV_DIST_LAPLACE = 0, 1
 DISTS = {"gauss": WV_DIST_GAUSS, "laplace": WV_DIST_LAPLACE}
 ERR_NAMES = {0: "WV_OK", -1: "WV_EINVAL", -2: "WV_ESHAPE", -3: "WV_EORDER", -4: "WV_EDEVICE",

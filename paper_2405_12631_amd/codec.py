@@ -81,12 +81,15 @@ class Graph:
 
 
 class Model:
-    """A model handle: weights uploaded and repacked on the current device."""
+    """A model handle: weights uploaded and repacked on the current device.
+
+    precision: WV_FP32, WV_BF16 or WV_FP8 context convs, `| WV_LIFT_SPLIT` for synthesis filters on
+    split 16-bit operands (about 2.5 times as fast, other last bits; see wv.h)."""
 
     def __init__(self, cfg, blob, precision=L.WV_FP32, device="cuda"):
         self.cfg = dict(cfg)
         self.c = make_config(cfg)
-        self.precision = precision
+        self.precision = precision & ~L.WV_LIFT_SPLIT   # of the context model, as a stream's header holds it
         blob = np.ascontiguousarray(blob, np.float32)
         n = ctypes.c_longlong()
         L.call("wv_weights_count", _byref(self.c), _byref(n))

@@ -541,8 +541,8 @@ static const int kArDx[12] = {-2, -1, 0, 1, 2, -2, -1, 0, 1, 2, -2, -1};
 // rounds the filter outputs and has to repeat the analysis bit for bit.
 static bool lift_splittable(const wv_config& c) { return c.lift_ch == 32 && c.lift_layers == 3 && !c.lift_int; }
 
-// Context layers are packed for the precision's kernel; lifting is always FP32, or split
-// operands of FP32 accuracy.
+// Context layers are packed for the precision's kernel; the lifting filters as FP32, and as split
+// operands too where the model's synthesis takes them.
 HostModel pack_all(PackBuf& pb, const float* blob, const wv_config& c, int precision) {
     const Manifest mf = make_manifest(c);
     HostModel hm;
@@ -552,9 +552,10 @@ HostModel pack_all(PackBuf& pb, const float* blob, const wv_config& c, int preci
         for (size_t l = 1; l + 1 < v.size(); ++l)
             hm.lift_mid[f].push_back(pack_mfma(pb, blob, v[l], 0, false, 0));
         hm.lift_last[f] = pack_vec_last(pb, blob, v.back());
-        if (lift_splittable(c)) hm.lift_split[f] = pack_lift_split(pb, blob, v[0], v[1], v[2]);
+        if (precision & WV_LIFT_SPLIT) hm.lift_split[f] = pack_lift_split(pb, blob, v[0], v[1], v[2]);
     }
-    auto ctxpack = precision == WV_BF16 ? pack_mfma16 : precision == WV_FP8 ? pack_mfma8 : pack_mfma;
+    const int ctx = precision & ~WV_LIFT_SPLIT;
+    auto ctxpack = ctx == WV_BF16 ? pack_mfma16 : ctx == WV_FP8 ? pack_mfma8 : pack_mfma;
     hm.lstm = ctxpack(pb, blob, mf.lstm, 1, true, c.ctx_ch);
     for (int t = 0; t < 4; ++t)
         for (int g = 0; g < 4; ++g) {
@@ -613,11 +614,11 @@ HostModel pack_all(PackBuf& pb, const float* blob, const wv_config& c, int preci
 
 struct wv_model {
     wv_config cfg;
-    int precision;
+    int precision;                       // of the context model
+    bool split;                          // synthesis filters on split operands (lift_split)
     VecLayer lift_first[4], lift_last[4];
     std::vector<MfmaLayer> lift_mid[4];
     LiftSplit lift_split[4];
-    bool split_ok;                       // lift_split is filled
     MfmaLayer lstm;                      // WV_FP32
     std::vector<MfmaLayer> ctx[4][4];
     MfmaLayer16 lstm16;                  // WV_BF16
@@ -631,6 +632,11 @@ struct wv_model {
 };
 
 static int check_precision(const wv_config* c, int precision) {
+    if (precision >= 0 && (precision & WV_LIFT_SPLIT)) {
+        if (!lift_splittable(*c))
+            return fail(WV_EUNSUPPORTED, "split lifting needs lift_ch 32, lift_layers 3 and lift_int 0");
+        precision &= ~WV_LIFT_SPLIT;
+    }
     if (precision == WV_FP32) return WV_OK;
     if (precision == WV_BF16 || precision == WV_FP8) {
         const char* nm = precision == WV_BF16 ? "BF16" : "FP8";
@@ -685,6 +691,11 @@ extern "C" int wv_model_create(const wv_config* cfg, const float* d_weights, lon
     HIPCHK(hipStreamSynchronize(s));
     PackBuf pb;
     HostModel hm = pack_all(pb, blob.data(), *cfg, precision);
+    const bool split = precision & WV_LIFT_SPLIT;
+    precision &= ~WV_LIFT_SPLIT;
+    for (int f = 0; split && f < 4; ++f)
+        if (!hm.lift_split[f].ok)
+            return fail(WV_EUNSUPPORTED, "split lifting needs finite filter weights of at most 2^24");
     if (pb.data.size() * sizeof(float) > pack_bytes)
         return fail(WV_ENOMEM, "pack buffer has %zu bytes, needs %zu", pack_bytes,
                     pb.data.size() * sizeof(float));
@@ -705,10 +716,9 @@ extern "C" int wv_model_create(const wv_config* cfg, const float* d_weights, lon
     wv_model* m = new wv_model();
     m->cfg = *cfg;
     m->precision = precision;
-    m->split_ok = lift_splittable(*cfg);
+    m->split = split;
     for (int f = 0; f < 4; ++f) {
         const SplitRef& sp = hm.lift_split[f];
-        m->split_ok = m->split_ok && sp.ok;
         m->lift_split[f] = LiftSplit{base + sp.w1, base + sp.w2, base + sp.w3, base + sp.b1, base + sp.b2, base + sp.b3,
                                      sp.s2, sp.s3};
         m->lift_first[f] = vec(hm.lift_first[f]);
@@ -864,11 +874,6 @@ enum { F_PROW = 0, F_UROW = 1, F_PCOL = 2, F_UCOL = 3 };
 
 inline View vw(float* p, long long ps, int rs, int cs) { return View{p, ps, rs, cs}; }
 inline CView cvw(const float* p, long long ps, int rs, int cs) { return CView{p, ps, rs, cs}; }
-
-// The split-operand filters for one synthesis: float results only.  Bytes stay those of the FP32
-// kernels, whose sums round differently (a rounding tie could fall the other way).
-// WV_LIFT_FORM names an FP32 form.
-bool use_split(const wv_model* m, const uint8_t* d_u8) { return m->split_ok && !d_u8 && !getenv("WV_LIFT_FORM"); }
 
 // out = A + sign * (predict ? z + N(z) : z/2 + N(z)) on an h x w array.
 int run_filter(const wv_model* m, int f, CView z, CView A, View out, int N, int h, int w,
@@ -1033,7 +1038,6 @@ static int synth_impl(const wv_model* m, const int16_t* d_q, const float* d_y, i
     float* lb = base + sc.lbuf;
     float* hb = base + sc.hbuf;
     const int J = m->cfg.levels;
-    const bool split = use_split(m, d_u8);
     const float* X = y + lay[0].off;
     long long xps = HW;
     for (int j = J; j >= 1; --j) {
@@ -1047,21 +1051,21 @@ static int synth_impl(const wv_model* m, const int16_t* d_q, const float* d_y, i
         const CView lh = cvw(y + sLH.off, HW, ws, 1), hh = cvw(y + sHH.off, HW, ws, 1);
         const LiftIO even[2] = {{lh, cvw(X, xps, ws, 1), vw(lb, bps, 2 * ws, 1)},
                                 {hh, cvw(y + sHL.off, HW, ws, 1), vw(hb, bps, 2 * ws, 1)}};
-        rc = run_filters(m, split, F_UCOL, even, 2, N, hs, ws, 0, -1.f, a1, a2, s);
+        rc = run_filters(m, m->split, F_UCOL, even, 2, N, hs, ws, 0, -1.f, a1, a2, s);
         if (rc) return rc;
         const LiftIO odd[2] = {{cvw(lb, bps, 2 * ws, 1), lh, vw(lb + ws, bps, 2 * ws, 1)},
                                {cvw(hb, bps, 2 * ws, 1), hh, vw(hb + ws, bps, 2 * ws, 1)}};
-        rc = run_filters(m, split, F_PCOL, odd, 2, N, hs, ws, 1, 1.f, a1, a2, s);
+        rc = run_filters(m, m->split, F_PCOL, odd, 2, N, hs, ws, 1, 1.f, a1, a2, s);
         if (rc) return rc;
         // inverse row step: even = l - U_row(h); odd = h + P_row(even)
         const int ho = 2 * hs, wo = 2 * ws;
         float* xo = (j == 1) ? d_xhat : base + ((j & 1) ? sc.Xa : sc.Xb);
         const long long ops = (long long)ho * wo;
         const LiftIO re = {cvw(hb, bps, ws, 1), cvw(lb, bps, ws, 1), vw(xo, ops, wo, 2)};
-        rc = run_filters(m, split, F_UROW, &re, 1, N, ho, ws, 0, -1.f, a1, a2, s);
+        rc = run_filters(m, m->split, F_UROW, &re, 1, N, ho, ws, 0, -1.f, a1, a2, s);
         if (rc) return rc;
         const LiftIO ro = {cvw(xo, ops, wo, 2), cvw(hb, bps, ws, 1), vw(xo + 1, ops, wo, 2)};
-        rc = run_filters(m, split, F_PROW, &ro, 1, N, ho, ws, 1, 1.f, a1, a2, s);
+        rc = run_filters(m, m->split, F_PROW, &ro, 1, N, ho, ws, 1, 1.f, a1, a2, s);
         if (rc) return rc;
         X = xo;
         xps = ops;

@@ -1,4 +1,5 @@
-// One predict/update filter application of the synthesis transform (Sec. 3.1), 32 channels:
+// One predict/update filter application of the synthesis transform (Sec. 3.1), 32 channels, of a model
+// made with WV_LIFT_SPLIT (every synthesis of it; the FP32 forms are lift_fused_k and lift_rows_k):
 //   out = A + sign * f,  f = z + N(z) (predict) or z/2 + N(z) (update),
 //   N = conv3x3(32 -> 1) . tanh . conv3x3(32 -> 32) . tanh . conv3x3(1 -> 32),
 // every conv zero-padded at the array border, with all three convs on the 16-bit matrix units
