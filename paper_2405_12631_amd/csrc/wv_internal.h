@@ -254,7 +254,8 @@ hipError_t launch_ar_decode(const ArModel& M, const ArStreams& S, int16_t* q, lo
 // arrays of at least LIFT_ROWS_MIN_STRIP_ROWS (strip x row) units.
 constexpr int LIFT_ROWS_OUTW = 124;
 constexpr long long LIFT_ROWS_MIN_STRIP_ROWS = 2048;
-// Both take one or two sets (io[0], io[1]) of N planes of one size, planes N on being the second's.
+// Both take one or two sets (io[0], io[1]) of N planes of one size, planes N on being the second's; the
+// second set's row and column strides are the first's (launch_lift_fused looks).
 hipError_t launch_lift_rows(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets,
                             int N, int h, int w, int nstrips, int predict, float sign, int lift_int, hipStream_t s);
 hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets,

@@ -67,8 +67,8 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
     constexpr int NZ = (ZH * ZW + NT - 1) / NT;
     float zv_next[NZ];
     auto load_z = [&](const Tile& T) {
-        const CView& z = T.n < N ? io0.z : io1.z;
-        const float* zp = z.p + (long long)(T.n < N ? T.n : T.n - N) * z.ps;
+        const CView& z = io0.z;
+        const float* zp = T.n < N ? z.p + (long long)T.n * z.ps : io1.z.p + (long long)(T.n - N) * io1.z.ps;
 #pragma unroll
         for (int k = 0; k < NZ; ++k) {
             const int i = tid + k * NT;
@@ -110,9 +110,11 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
 
   for (int t = blockIdx.x; t < total; t += gridDim.x) {
     const Tile T = tile_of(t);
-    const int n = T.n < N ? T.n : T.n - N, r0 = T.r0, c0 = T.c0;
-    const CView& A = T.n < N ? io0.A : io1.A;
-    const View& out = T.n < N ? io0.out : io1.out;
+    const int r0 = T.r0, c0 = T.c0;
+    const bool second = T.n >= N;
+    const int n = T.n - (second ? N : 0);
+    const float* ap = (second ? io1.A.p : io0.A.p) + (long long)n * (second ? io1.A.ps : io0.A.ps);
+    float* op = (second ? io1.out.p : io0.out.p) + (long long)n * (second ? io1.out.ps : io0.out.ps);
     __syncthreads();   // the previous tile is done with zs and act (and the weights are in LDS)
 #pragma unroll
     for (int k = 0; k < NZ; ++k)
@@ -127,7 +129,7 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
         const int r = r0 + o / OW, c = c0 + o % OW;
         apre[j] = 0.f;
         if (((j * NT + tid) & 1) == 0 && r < h && c < w)
-            apre[j] = A.p[(long long)n * A.ps + (long long)r * A.rs + (long long)c * A.cs];
+            apre[j] = ap[(long long)r * io0.A.rs + (long long)c * io0.A.cs];
     }
 
     // layer 1 on the (OH+4) x (OW+4) region: tanh(b1 + sum_tap w1 z), zero outside the array.
@@ -264,7 +266,7 @@ __global__ __launch_bounds__(64 * NWV) void lift_fused_k(const VecLayer L1, cons
             const float zz = zs[(oy + 3) * ZW + ox + 3];
             float f = predict ? zz + v : 0.5f * zz + v;
             if (lift_int) f = rintf(f);
-            out.p[(long long)n * out.ps + (long long)r * out.rs + (long long)c * out.cs] = apre[j] + sign * f;
+            op[(long long)r * io0.out.rs + (long long)c * io0.out.cs] = apre[j] + sign * f;
         }
     }
   }
@@ -307,7 +309,12 @@ hipError_t lift_launch(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& 
 hipError_t launch_lift_fused(const VecLayer& L1, const MfmaLayer& L2, const VecLayer& L3, const LiftIO* io, int sets,
                              int N, int h, int w, int predict, float sign, int lift_int, hipStream_t s) {
     if ((long long)N * h * w == 0) return hipSuccess;
-    if (sets == 2 && (long long)N * h * w >= 1ll << 31) {   // the launches count tiles in 31 bits
+    // One by one where the launch would count its tiles in more than 31 bits, or where the sets' strides
+    // differ: the kernels take them from the first set (selected per item like the pointers, they cost
+    // spilled scalars: 8 planes of 1088 x 1920 in row form 10.46 ms a synthesis against 9.76).
+    auto same = [](const auto& a, const auto& b) { return a.rs == b.rs && a.cs == b.cs; };
+    if (sets == 2 && ((long long)N * h * w >= 1ll << 31 || !same(io[0].z, io[1].z) || !same(io[0].A, io[1].A) ||
+                      !same(io[0].out, io[1].out))) {
         const hipError_t e = launch_lift_fused(L1, L2, L3, io, 1, N, h, w, predict, sign, lift_int, s);
         return e != hipSuccess ? e : launch_lift_fused(L1, L2, L3, io + 1, 1, N, h, w, predict, sign, lift_int, s);
     }

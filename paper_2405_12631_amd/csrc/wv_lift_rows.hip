@@ -170,13 +170,13 @@ __device__ __forceinline__ void vec_role(const VecLayer& L3, const LiftIO& io0, 
     for (long long it = blockIdx.x; it < total; it += gridDim.x) {
         const Item I = item_of(it, nstrips, nseg, seg_rows, h);
         const int T = I.R + 10;
-        const LiftIO& io = I.n < N ? io0 : io1;
-        const CView &z = io.z, &A = io.A;
-        const View& out = io.out;
-        const int n = I.n < N ? I.n : I.n - N;
-        const float* zp = z.p + (long long)n * z.ps;
-        const float* ap = A.p + (long long)n * A.ps;
-        float* op = out.p + (long long)n * out.ps;
+        const bool second = I.n >= N;   // the strides are both sets'
+        const int n = I.n - (second ? N : 0);
+        const CView &z = io0.z, &A = io0.A;
+        const View& out = io0.out;
+        const float* zp = (second ? io1.z.p : z.p) + (long long)n * (second ? io1.z.ps : z.ps);
+        const float* ap = (second ? io1.A.p : A.p) + (long long)n * (second ? io1.A.ps : A.ps);
+        float* op = (second ? io1.out.p : out.p) + (long long)n * (second ? io1.out.ps : out.ps);
         auto zload = [&](int r) {   // z row r at column c0 - 3 + v (lanes 0 .. ZN - 1)
             const int c = I.c0 - 3 + v;
             return (v < ZN && r >= 0 && r < h && c >= 0 && c < w) ? zp[(long long)r * z.rs + (long long)c * z.cs] : 0.f;
