@@ -56,7 +56,10 @@ typedef _Float16 halfx2 __attribute__((ext_vector_type(2)));
 typedef float floatx16 __attribute__((ext_vector_type(16)));
 
 constexpr int NW = 4;             // waves of a workgroup; G of them share a strip
-constexpr float ZMAX = 7.9e28f;   // |z| beyond this saturates every tanh; keeps layer 1 finite
+// Layer 1 takes z clamped to this, so that no product or sum of its split parts overflows (weights are
+// at most 2^24): infinite z saturates the tanhs that its weights' signs say, where an FP32 sum of
+// opposite infinities is NaN.  (A weight below 1e-28 does not saturate its tanh at the clamp.)
+constexpr float ZMAX = 7.9e28f;
 
 template <int G>
 struct Strip {

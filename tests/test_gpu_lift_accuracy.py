@@ -74,3 +74,29 @@ def test_filters_beyond_the_split_range_are_refused():
             codec.Model(cfg, pack_weights(cfg, w), precision=WV_LIFT_SPLIT)
     w["lift.U_row.2.b"].flat[0] = 2.0 ** 24
     codec.Model(cfg, pack_weights(cfg, w), precision=WV_LIFT_SPLIT)
+
+
+def test_split_operands_saturate_on_infinite_subbands():
+    """Infinite and huge values: split operands saturate the filters they reach, so that no value is lost
+    that FP32 keeps finite, and NaN stays NaN.  Opposite infinities side by side, where an FP32 sum is NaN,
+    keep a finite filter value."""
+    need_gpu()
+    from paper_2405_12631_amd import codec, WV_FP32, WV_LIFT_SPLIT
+    say("split operands and infinities")
+    cfg, (H, W) = get_config("ycbcr512x768"), (96, 160)
+    blob = pack_weights(cfg, make_weights(cfg))
+    y = torch.from_numpy(np.random.default_rng(8).normal(0, 20, (4, H * W)).astype(np.float32)).cuda()
+    inf = float("inf")
+    out = []
+    for prec in (WV_FP32, WV_FP32 | WV_LIFT_SPLIT):
+        model = codec.Model(cfg, blob, precision=prec)
+        ws = codec.Workspace(model, 4, H, W)
+        at = ws.lay[-2]["offset"] + 20 * ws.lay[-2]["w"] + 30          # LH of level 1
+        y[0, at], y[1, at], y[1, at + 1], y[2, at], y[3, at] = inf, inf, -inf, 3e38, float("nan")
+        out.append(codec.synthesize(model, ws, y=y)[0])
+    fp32, split = out
+    assert bool((torch.isfinite(split) | ~torch.isfinite(fp32)).all())
+    assert int(torch.isnan(split[1]).sum()) < int(torch.isnan(fp32[1]).sum())
+    assert torch.equal(torch.isnan(split[3]), torch.isnan(fp32[3])) and bool(torch.isnan(fp32[3]).any())
+    near = torch.isfinite(fp32) & (fp32.abs() < 1e4)
+    assert float((split - fp32)[near].abs().max()) <= 1e-3
