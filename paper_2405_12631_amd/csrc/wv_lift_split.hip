@@ -405,17 +405,17 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
 }
 
 template <int G>
-int split_resident() {   // resident workgroups, cached per device (0: unknown)
+int split_resident() {   // resident workgroups, cached per device (256 if unknown: the cut, not the results, depends on it)
     static std::atomic<int> cache[64];
     int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
     int n = cache[dev].load(std::memory_order_relaxed);
     if (n == 0) {
         int per_cu = 0, cus = 0;
         if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess ||
             hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, lift_split_k<G>, 64 * NW, 0) != hipSuccess ||
             per_cu < 1)
-            return 0;
+            return 256;
         n = per_cu * cus;
         cache[dev].store(n, std::memory_order_relaxed);
     }
@@ -433,7 +433,6 @@ template <int G>
 Cut split_cut(int h, int w, long long planes) {
     Cut c{};
     const long long slots = (long long)split_resident<G>() * (NW / G);
-    if (slots < 1) return c;
     c.nstrips = (w + Strip<G>::OUTW - 1) / Strip<G>::OUTW;
     const long long cols = c.nstrips * planes;
     for (int ns = 1; ns <= h; ++ns) {
@@ -459,7 +458,6 @@ hipError_t launch_lift_split(const LiftSplit& L, const LiftIO& io0, const LiftIO
     if ((long long)N * h * w == 0) return hipSuccess;
     if (sets < 1 || sets > 2) return hipErrorInvalidValue;
     const Cut c1 = split_cut<1>(h, w, (long long)N * sets), c4 = split_cut<NW>(h, w, (long long)N * sets);
-    if (c1.grid < 1 || c4.grid < 1) return hipErrorInvalidDevice;
     if (c1.total >= 1ll << 31 || c4.total >= 1ll << 31) return hipErrorInvalidValue;
     if (c1.cost < c4.cost)
         hipLaunchKernelGGL(lift_split_k<1>, dim3(c1.grid), dim3(64 * NW), 0, s, L, io0, io1, N, h, w, c1.nstrips,
