@@ -42,6 +42,7 @@
 // segment, so results do not depend on the launch geometry or on the other planes.
 #include "wv_device.h"
 #include "wv_internal.h"
+#include "wv_pieces.h"
 #include "wv_rows.h"
 
 #include <algorithm>
@@ -435,16 +436,14 @@ Cut split_cut(int h, int w, long long planes) {
     const long long slots = (long long)split_resident<G>() * (NW / G);
     c.nstrips = (w + Strip<G>::OUTW - 1) / Strip<G>::OUTW;
     const long long cols = c.nstrips * planes;
-    for (int ns = 1; ns <= h; ++ns) {
-        const int r = (h + ns - 1) / ns;
+    each_segment_rows(h, [&](int r) {
         const long long items = cols * ((h + r - 1) / r);
         const long long cost = (items + slots - 1) / slots * (r + 6) * (2 * items <= slots ? 3 : 4);
         if (c.cost == 0 || cost < c.cost) {
             c.cost = cost;
             c.seg_rows = r;
         }
-        if (r == 1) break;
-    }
+    });
     c.nseg = (h + c.seg_rows - 1) / c.seg_rows;
     c.total = cols * c.nseg;
     c.grid = (int)((std::min(c.total, slots) + NW / G - 1) / (NW / G));

@@ -16,6 +16,18 @@ inline int stack_seg_rows(int h, int cap = 128) {
     return (h + pieces - 1) / pieces;
 }
 
+// f(r) for every segment length r = ceil(h / ns) that some number of segments ns of h rows gives, the
+// longest first: about 2 sqrt(h) calls.
+template <class F>
+void each_segment_rows(int h, const F& f) {
+    for (int ns = 1; ns <= h;) {
+        const int r = (h + ns - 1) / ns;
+        f(r);
+        if (r == 1) break;
+        ns = (h + r - 2) / (r - 1);   // the least ns whose segments are shorter
+    }
+}
+
 // The piece cap of a fused launch over several plane groups' subbands ({h, w, planes} each):
 // the one among a few candidates that minimises the most row steps a resident workgroup walks.
 // Items are dealt round-robin over min(items, resident) workgroups in the kernels' order (strip
