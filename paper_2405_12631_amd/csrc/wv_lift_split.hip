@@ -229,7 +229,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
         for (int i = 0; i < 16; ++i) A0[i] = A1[i] = A2[i] = 0.f;
         float ua0 = 0.f, ua1 = 0.f, ub0 = 0.f, ub1 = 0.f;   // layer-3 sums of the next two output rows
         auto step = [&](int t, auto on) {   // on: layers 1 and 2 run
-
             if (t >= 11 && owner) at(op + (long long)(y0 - 11 + t) * ors, oo) = pend;
             // z row y0 - 3 + t, loaded in the previous step; then the next step's z and A
             auto turn = [&](float s, float zz) {
@@ -254,8 +253,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
             } else {
                 // One straight block: 63 MFMAs with the vector work of the finished layer-2 row and of
                 // layer 1 between them.  Steps outside a stage's rows compute values that no needed row
-                // takes; the first step has layer 1 only, the last two neither layer 1 nor layer 2.
-                auto block = [&](auto do1, auto do2, auto do3) {
+                // takes; the last two steps have neither layer 1 nor layer 2 (`on`).
                 const int r = y0 - 10 + t;   // output row, from the layer-3 sums of the previous step
                 const float(*Sr)[SL] = S.sx[(r2 - 1) & 1];
                 float s0 = Sr[0][p], s1 = Sr[1][p + 1], s2 = Sr[2][p + 2];
@@ -326,22 +324,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                     constexpr int sl = slot;
                     // operands are read from LDS several slots before their MFMAs
                     if constexpr (sl == 1 || sl == 2) load_b2(sl + 1);
-                    if constexpr (do2 && sl == 3) load_hi(0);
-                    if constexpr (do2 && sl >= 5) {
+                    if constexpr (on && sl == 3) load_hi(0);
+                    if constexpr (on && sl >= 5) {
                         constexpr int i = sl - 5, dx = i / 18, j = i % 18;
                         if constexpr (j < 3 || (j >= 6 && j < 9)) wl[j % 3] = W.w2l[3 * (2 - j % 3) + dx][j / 6][lane];
                         if constexpr (j == 5) load_lo(dx);
                         if constexpr (j == 13 && dx < 2) load_hi(dx + 1);
                     }
-                    if constexpr (do3 && sl == 27) {
+                    if constexpr (sl == 27) {
                         w3f[0] = W.w3[0][lane];
                         w3f[1] = W.w3[1][lane];
                     }
                     if constexpr (sl < 5) {
-                        if constexpr (do1) a1 = mfma_bf16w(wf1[sl % 2], zf1[sl % 2], a1);
+                        if constexpr (on) a1 = mfma_bf16w(wf1[sl % 2], zf1[sl % 2], a1);
                         pin(a1);
-                        if constexpr (do1 && sl < 3) load_1(std::integral_constant<int, sl + 2>{});
-                    } else if constexpr (do2) {
+                        if constexpr (on && sl < 3) load_1(std::integral_constant<int, sl + 2>{});
+                    } else if constexpr (on) {
                         constexpr int i = sl - 5, dx = i / 18, j = i % 18, g = j / 3, k = j % 3;
                         // K chunk 0's high x high and low x high, chunk 1's, then both high x low
                         constexpr int pr = g >= 4 ? 2 : g & 1, c = g >= 4 ? g - 4 : g >> 1;
@@ -361,11 +359,11 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                     constexpr int e = sl + 1;
                     constexpr int u1 = e < 5 ? (16 * e) / 5 : e < 30 ? 16 + (64 * (e - 5)) / 25 : 80 + (80 * (e - 30)) / 29;
                     static_for<u0, u1>([&](auto k) {
-                        if constexpr (k < 80 ? do3 : do1) unit(k);
+                        if constexpr (k < 80 || on) unit(k);
                     });
                     if constexpr (sl == 6) s0 = (s0 + s1) + s2;
                     if constexpr (sl == 44) turn(s0, zz);
-                    if constexpr (do3 && sl == 30) {
+                    if constexpr (sl == 30) {
                         hi[0] = make_uint4(hw[0], hw[1], hw[2], hw[3]);
                         hi[1] = make_uint4(hw[4], hw[5], hw[6], hw[7]);
                         lo[0] = make_uint4(lw[0], lw[1], lw[2], lw[3]);
@@ -373,10 +371,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                         const floatx16 zero = {0.f};
                         tt = mfma_f16(w3f[0], hi[0], zero);
                     }
-                    if constexpr (do3 && sl == 31) tt = mfma_f16(w3f[1], hi[1], tt);
-                    if constexpr (do3 && sl == 32) tt = mfma_f16(w3f[0], lo[0], tt);
-                    if constexpr (do3 && sl == 33) tt = mfma_f16(w3f[1], lo[1], tt);
-                    if constexpr (do3 && sl == 38) {   // rows 0-2 (and 16-18: the weights' low parts) of the wave half: a column's taps
+                    if constexpr (sl == 31) tt = mfma_f16(w3f[1], hi[1], tt);
+                    if constexpr (sl == 32) tt = mfma_f16(w3f[0], lo[0], tt);
+                    if constexpr (sl == 33) tt = mfma_f16(w3f[1], lo[1], tt);
+                    if constexpr (sl == 38) {   // rows 0-2 (and 16-18: the weights' low parts) of the wave half: a column's taps
                         float* so = &S.sx[r2 & 1][half][1 + p];
                         so[0] = ua0 + (tt[2] + tt[10]);
                         ua0 = ua1 + (tt[1] + tt[9]);
@@ -389,12 +387,10 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(2))) vo
                 });
 #pragma unroll
                 for (int c = 0; c < 2; ++c) {
-                    if (!do1) continue;
+                    if (!on) continue;
                     S.ah[r1 & 1][c][1 + p][half] = make_uint4(hw[4 * c], hw[4 * c + 1], hw[4 * c + 2], hw[4 * c + 3]);
                     S.al[r1 & 1][c][1 + p][half] = make_uint4(lw[4 * c], lw[4 * c + 1], lw[4 * c + 2], lw[4 * c + 3]);
                 }
-                };
-                block(on, on, std::true_type{});
             }
             strip_sync<G>();
         };
