@@ -4,7 +4,8 @@
 //   N = conv3x3(32 -> 1) . tanh . conv3x3(32 -> 32) . tanh . conv3x3(1 -> 32),
 // every conv zero-padded at the array border, with all three convs on the 16-bit matrix units
 // at no less than FP32 accuracy: each FP32 operand is split into 16-bit parts whose products are
-// exact in the FP32 accumulator, and the products that matter are all taken.
+// exact in the FP32 accumulator, and the products that matter are all taken (three BF16 parts: Henry,
+// Tang, Heinecke, ARITH 2019; two FP16 parts with power-of-two scaling: Ootomo, Yokota, IJHPCA 2022).
 //   layer 1: z and w as three BF16 parts each (24 bits, the FP32 range); 8 of the 9 products, one
 //            tap per wave half: 5 MFMAs for 9 taps;
 //   layer 2: the tanh outputs (in [-1, 1], scaled by 2^10) and the weights (scaled by a power of
@@ -12,8 +13,9 @@
 //            MFMAs of K = 16 per tap;
 //   layer 3: the same split; the MFMA's rows are the nine taps (T[tap][position]), and an output
 //            is the sum of nine of them.
-// Error against 64 bits over a 512 x 768 and a 1088 x 1920 synthesis: 3.46e-8 and 4.38e-8 of the
-// norm, the same as with the FP32 matrix units (lift_fused_k, lift_rows_k).
+// Error against 64 bits over a 512 x 768 and a 1088 x 1920 synthesis: 3.48e-8 and 4.30e-8 of the
+// norm, the same as with the FP32 matrix units (lift_fused_k, lift_rows_k), and at most 0.6 % above
+// theirs for filters of other scales (tests/test_gpu_lift_accuracy.py).
 //
 // What bounds it.  Per 32 positions 63 v_mfma_f32_32x32x16 (32 cycles each) against 578 FP32
 // MFMA-equivalents before, and about 240 vector instructions, 64 of them exponentials and

@@ -26,3 +26,12 @@ def test_no_scalar_spills(src, kernels, tmp_path):
     kernels."""
     spills = re.findall(r"\.sgpr_spill_count:\s*(\d+)", _listing(src, tmp_path))
     assert spills == ["0"] * kernels, spills
+
+
+@pytest.mark.slow
+def test_split_kernel_uses_global_memory_and_no_scratch(tmp_path):
+    """Both strip forms of the split kernel sit at the edge of the register file (251 and 255 VGPRs)."""
+    asm = _listing("wv_lift_split.hip", tmp_path)
+    assert re.findall(r"; ScratchSize: (\d+)", asm) == ["0", "0"]
+    assert re.findall(r"\.(?:v|s)gpr_spill_count:\s*(\d+)", asm) == ["0"] * 4
+    assert asm.count("global_load") > 20 and not re.search(r"^\s*(flat|scratch)_", asm, flags=re.M)
