@@ -12,17 +12,21 @@
 //     (F_j = F_max - ceil(F_max * (1 - C_j)), at least one count below F_max),
 //     so no digits are lost to 1 - tiny rounding to 1;
 //   * a running maximum makes the row non-decreasing.
-// What bounds it: outside the rows' windows only the writes (260 bytes a row), inside them the
-// tails, about 50 vector instructions per component and entry.  Windows differ: for scales spread
-// over a decade their mean is 25 entries, but the longest of 64 rows has 101.  So a workgroup
-// fills its rows' entries outside the windows in LDS, deals all the window entries evenly to its
-// threads (a prefix sum of the window lengths, a binary search per entry), and copies the rows out
-// as one block.  (One thread or four lanes per row, as before, step through the longest window of a
-// wave: 2.4 M such rows 1239 us, 1152 rows 27 us; now 335 us and 5 us.  For rows as narrow as an
-// untrained model's, ten entries each, the search and the fill cost as much as the even deal saves: a
-// batch of 8 Mpixels 2.25 and 2.26 ms, one of 51 Mpixels 9.6 before and 11.0 now, 4.1 TB/s.  128 or 512
-// threads, or 32 rows, 11.3 to 13.8.)  The running maximum is the identity up to rounding, so entries are
-// only compared with their predecessors, and a row is gone through again if one of them is larger.
+// What bounds it: vector instructions, about 230 per window entry and 6 per pair of entries filled, and for
+// narrow windows the writes (260 bytes a row).  Windows differ: for scales spread over a decade
+// their mean is 25 entries, but the longest of 64 rows has 101.  So a workgroup fills its rows' entries
+// outside the windows in LDS, deals all the window entries evenly to its threads (a prefix sum of the
+// window lengths, a binary search per entry), and copies the rows out as one block.  (One thread or four
+// lanes per row step through the longest window of a wave.)  An untrained model's rows all have six
+// entries: where a workgroup's windows are of one length, a multiplication takes the search's place.
+//   rows (scales)                 a thread or 4 lanes per row   now
+//   9.6 M (six entries all)             564 us                  573 us, 5.0 TB/s
+//   9.6 M (0.7, spread by 15 %)         706                     646
+//   2.4 M (over a decade)              1234                     322
+//   1152 (over a decade)                 31                     4.8
+// 128 or 512 threads, or 32 rows, were 10 to 20 % slower, four lanes per row with its values in registers
+// 8 %.  The running maximum is the identity up to rounding, so entries are only compared with their
+// predecessors, and a row is gone through again if one of them is larger.
 #include "wv_device.h"
 #include "wv_internal.h"
 
@@ -37,11 +41,13 @@ constexpr int MAXE = 256;   // max entries per row (N_s + 1)
 template <int K, int DIST, int ROWS>
 __global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, long long n, int smin, int nsym,
                                            uint16_t* __restrict__ out) {
+    constexpr bool BIG = ROWS == 64;
     extern __shared__ __attribute__((aligned(16))) uint16_t tab[];   // [ROWS][nsym + 1]
     __shared__ CdfRow<K, DIST> R[ROWS];
     __shared__ int win[ROWS][2];        // evaluated entries j1 <= j < j2
     __shared__ int first[ROWS + 1];     // of a row's entries among the workgroup's
     __shared__ int bad[ROWS], anybad;   // rows whose F decreases somewhere
+    __shared__ int common;              // the rows' window length if they have one, else 0
     const int tid = threadIdx.x, lane = tid & 63;
     const int E = nsym + 1;
     const long long row0 = (long long)blockIdx.x * ROWS;
@@ -70,47 +76,62 @@ __global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, lo
         }
         if (tid < ROWS) first[tid + 1] = sum;
         if (tid == 0) first[0] = anybad = 0;
+        if (BIG) {
+            const bool same = __all(len == __builtin_amdgcn_readfirstlane(len));
+            if (tid == 0) common = same ? len : 0;
+        }
     }
     __syncthreads();
     const int Fmax = 65536 - nsym;
     {   // cdf[j] = j below the window, j + F_max - 1 above it; the last entry 0 (a thread keeps its row)
-        const int r = tid % ROWS, j2 = win[r][1];
-        if ((E & 1) == 0) {
-            uint32_t* w = reinterpret_cast<uint32_t*>(tab + r * E);
-            for (int q = tid / ROWS; q < E / 2; q += NT / ROWS) {
-                const int j = 2 * q;
-                const uint32_t a = j + (j >= j2 ? Fmax - 1 : 0), b = j + 1 + (j + 1 >= j2 ? Fmax - 1 : 0);
-                w[q] = (a & 0xffffu) | (j + 1 == nsym ? 0u : b << 16);
-            }
+        const int r = tid % ROWS, q0 = tid / ROWS, j2 = win[r][1];
+        if ((E & 1) == 0) {   // two entries at a time; the window's last one, beside the first above it, is replaced below
+            uint32_t* w = reinterpret_cast<uint32_t*>(tab) + r * (E / 2);
+            const uint32_t above = 0x10001u * (uint32_t)(Fmax - 1);
+            uint32_t v = 0x20002u * q0 + 0x10000u;
+#pragma unroll 4
+            for (int q = q0; q < E / 2; q += NT / ROWS, v += 0x20002u * (NT / ROWS)) w[q] = v + (q >= (j2 >> 1) ? above : 0u);
         } else {
-            for (int j = tid / ROWS; j < E; j += NT / ROWS)
-                tab[r * E + j] = j == nsym ? (uint16_t)0 : (uint16_t)(j + (j >= j2 ? Fmax - 1 : 0));
+            for (int j = q0; j < nsym; j += NT / ROWS) tab[r * E + j] = (uint16_t)(j + (j >= j2 ? Fmax - 1 : 0));
         }
     }
     __syncthreads();
-    const int total = first[ROWS];
-    for (int e0 = tid - lane; e0 < total; e0 += NT) {
-        const int e = min(e0 + lane, total - 1);
-        int r = 0;
+    if (tid < ROWS) {
+        tab[tid * E + nsym] = 0;
+        const int j2 = win[tid][1];
+        if (win[tid][0] == j2) tab[tid * E + j2 - 1] = (uint16_t)(j2 - 1);   // an empty window: below it
+    }
+    const int total = first[ROWS], len = BIG ? common : 0;
+    const float per = __builtin_amdgcn_rcpf((float)len);
+    auto locate = [&](int e, int& r, int& i) {   // entry e is entry i of row r's window
+        if (BIG && len) {
+            r = (int)(((float)e + 0.5f) * per);   // exact: e < 2^14, so the product is 1/512 or more from a whole number
+            i = e - r * len;
+            return;
+        }
+        r = 0;
 #pragma unroll
         for (int d = ROWS / 2; d >= 1; d >>= 1)   // last row with first[r] <= e
             if (first[r + d] <= e) r += d;
-        const int f = first[r], j1 = win[r][0], j = j1 + e - f;
+        i = e - first[r];
+    };
+    for (int e0 = tid - lane; e0 < total; e0 += NT) {
+        int r, i;
+        locate(min(e0 + lane, total - 1), r, i);
+        const int j = win[r][0] + i;
         const CdfRow<K, DIST> row = R[r];
         const int F = max(cdf_F_in<K, DIST>(row, j), 0);
         tab[r * E + j] = (uint16_t)(j + F);
         // the row's entry before this one, except for the first lane (checked below)
         const int before = __builtin_amdgcn_update_dpp(0, F, 0x138, 0xf, 0xf, false);   // wave_shr:1
-        if (lane > 0 && e > f && F < before) bad[r] = anybad = 1;
+        if (lane > 0 && i > 0 && F < before) bad[r] = anybad = 1;
     }
     __syncthreads();
     for (int e = 64 * tid; e < total; e += 64 * NT) {   // entries that a first lane evaluated
-        int r = 0;
-#pragma unroll
-        for (int d = ROWS / 2; d >= 1; d >>= 1)
-            if (first[r + d] <= e) r += d;
-        const uint16_t* c = tab + r * E + win[r][0] + e - first[r];
-        if (e > first[r] && c[0] <= c[-1]) bad[r] = anybad = 1;
+        int r, i;
+        locate(e, r, i);
+        const uint16_t* c = tab + r * E + win[r][0] + i;
+        if (i > 0 && c[0] <= c[-1]) bad[r] = anybad = 1;
     }
     __syncthreads();
     if (anybad) {
@@ -127,9 +148,11 @@ __global__ __launch_bounds__(NT) void cdf_k(const float* __restrict__ params, lo
     uint16_t* dst = out + row0 * E;
     const int nel = nrows * E;
     if ((((uintptr_t)dst) & 15) == 0 && (nel & 7) == 0) {
-        const uint4* src4 = reinterpret_cast<const uint4*>(tab);
-        uint4* dst4 = reinterpret_cast<uint4*>(dst);
-        for (int i = tid; i < nel / 8; i += NT) dst4[i] = src4[i];
+        char* base = reinterpret_cast<char*>(dst);
+        const char* from = reinterpret_cast<const char*>(tab);
+#pragma unroll 4
+        for (uint32_t o = 16 * tid; o < 2u * nel; o += 16 * NT)
+            st_g(reinterpret_cast<uint4*>(base + o), *reinterpret_cast<const uint4*>(from + o));
     } else {
         for (int i = tid; i < nel; i += NT) dst[i] = tab[i];
     }
@@ -141,10 +164,11 @@ hipError_t launch_cdf(const float* params, long long n, int K, int dist, int smi
                       uint16_t* cdf, hipStream_t s) {
     if (n == 0) return hipSuccess;
     if (nsym + 1 > MAXE || nsym < 2) return hipErrorInvalidValue;
-    // 64 rows per workgroup share the fixed work best; up to about 100 000 rows (1500 such workgroups,
-    // six per CU) 16 rows finish sooner: 1152 rows 5.1 against 9.4 us, 74 000 rows 18.0 against
-    // 18.8 us, 150 000 rows 30.4 against 28.8 us.
-    const bool small = n <= 96 * 1024;
+    // 64 rows per workgroup share the fixed work best, but in 16-row workgroups few rows are on more CUs.
+    // 16 against 64, scales over a decade: 1152 rows 4.8 and 8.3 us, 18 432 7.5 and 10.4, 49 152 13.4 and
+    // 13.7, 98 304 21.5 and 19.8; all windows six entries: 1152 3.7 and 4.3, 18 432 5.1 and 5.3, 49 152 8.9
+    // and 6.9, 98 304 14.4 and 9.3.
+    const bool small = n <= 40 * 1024;
     const int rows = small ? 16 : 64;
     const unsigned g = (unsigned)((n + rows - 1) / rows);
     const size_t lds = ((size_t)rows * (nsym + 1) * sizeof(uint16_t) + 15) & ~(size_t)15;
