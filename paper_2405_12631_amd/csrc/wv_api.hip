@@ -1488,20 +1488,6 @@ struct PlanLaunch {
     int has_sym = 0;
 };
 
-// Compute units of the current device, cached per device: the grid of the persistent fused
-// launches, which keep one workgroup per compute unit.
-int device_cus() {
-    static std::atomic<int> cache[64];
-    int dev = 0;
-    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
-    int n = cache[dev].load(std::memory_order_relaxed);
-    if (n == 0) {
-        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
-        cache[dev].store(n, std::memory_order_relaxed);
-    }
-    return n;
-}
-
 // Whether a model's step stacks can run as one fused launch per step (wv_stack_bf16.hip):
 // BF16, 64 channels, three ReLU layers and the head, the head's 3K outputs in one
 // 16-column block.  WV_FUSED_STACKS=0 keeps the layer-by-layer launches (tests compare

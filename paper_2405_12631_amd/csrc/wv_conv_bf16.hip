@@ -494,13 +494,15 @@ hipError_t launch_t(const MfmaLayer16& L, const ConvArgs& a0, hipStream_t s) {
     const int ncols = (MODE == CONV_HEAD) ? 1 : L.nbt / NB;
     dim3 grid((unsigned)(a.tiles_x * a.tiles_y * a.N * ncols));
     // All weights before the loop, where latency counts: a tap of one or two blocks computes for 60 to
-    // 250 cycles, so slices read two taps ahead are waited for at every tap.  Up to one workgroup a CU
-    // that costs nothing; up to two (2.3) rounds of one where two still fit a CU.  A 512 x 768 image's
-    // launches of 36 to 252 workgroups went from 7.6 to 7.0 us, the decode from 4.44 to 4.35 ms (FP8: 3.43
-    // to 3.35); beyond these lines the copy of 36 KB is exposed instead (all that fit: FP8 3.55 ms; up to
-    // 600 workgroups that do not fit twice: BF16 4.63).
-    constexpr bool FITS = Geo<CIN, NB, SYM, MODE, F8>::ALL_FITS;
-    if (grid.x <= 256 || (FITS && grid.x <= 600))
+    // 250 cycles, so slices read two taps ahead are waited for at every tap.  What it gives, by workgroups
+    // per CU (times with / without):
+    //   up to one: 0.93 (BF16, two blocks), 0.90 (with symbols), 0.93 (FP8), 0.97 (head), 0.99 (ConvLSTM);
+    //   up to two, where one no longer fits beside another: 1.23 to 1.33; where two do: 0.94 to 0.99 (FP8, two
+    //     blocks), 0.98 (head), 1.00 (FP8 ConvLSTM);
+    //   up to three, where two fit: 0.95 to 0.97 (FP8, two blocks), 0.95 to 0.97 (head), 1.20 (FP8 ConvLSTM,
+    //     four blocks); beyond: 1.05 (FP8, 3.5 per CU), 1.20.
+    constexpr int PER_CU = !Geo<CIN, NB, SYM, MODE, F8>::ALL_FITS ? 1 : NB == 4 ? 2 : 3;
+    if ((long long)grid.x <= (long long)PER_CU * device_cus())
         hipLaunchKernelGGL((conv3x3_mfma_bf16<CIN, NB, SYM, MODE, F8, true>), grid, dim3(256), 0, s, L, a);
     else
         hipLaunchKernelGGL((conv3x3_mfma_bf16<CIN, NB, SYM, MODE, F8, false>), grid, dim3(256), 0, s, L, a);

@@ -5,9 +5,25 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include <atomic>
+
 #include "../../include/wv.h"
 
 namespace wv {
+
+// Compute units of the current device, cached per device (256 if unknown): the grid of the persistent
+// fused launches, which keep one workgroup per compute unit, and the unit of rules on workgroup counts.
+inline int device_cus() {
+    static std::atomic<int> cache[64];
+    int dev = 0;
+    if (hipGetDevice(&dev) != hipSuccess || dev < 0 || dev >= 64) return 256;
+    int n = cache[dev].load(std::memory_order_relaxed);
+    if (n == 0) {
+        if (hipDeviceGetAttribute(&n, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || n < 1) n = 256;
+        cache[dev].store(n, std::memory_order_relaxed);
+    }
+    return n;
+}
 
 // Strided 2-D view of a stack of planes: element (n, r, c) lives at
 // p[n * ps + r * rs + c * cs].  Used to read even/odd samples of a plane
