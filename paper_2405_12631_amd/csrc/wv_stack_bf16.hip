@@ -111,14 +111,15 @@ struct Smem {
 // 16 bytes per active lane from byte voff of the row at `row` (of `bytes` bytes; the buffer's bounds
 // check gives zeros outside them) straight into LDS at lds + 16 lane.  The caller waits (wait_vm) before
 // the barrier that publishes them; in the builtin's place, the compiler would wait before the next LDS
-// read of any kind.  The s_nop covers the wait states after writes of m0 and of the descriptor.
+// read of any kind.  The LDS address is an operand in m0, which the compiler sets and so knows of; the
+// s_nop covers the wait states after writes of m0 and of the descriptor.
 __device__ __forceinline__ void row_to_lds(const void* row, uint32_t bytes, uint32_t voff, uint32_t lds) {
     typedef int int4v __attribute__((ext_vector_type(4)));
     const uint64_t a = (uint64_t)row;
     const int4v rsrc = {__builtin_amdgcn_readfirstlane((int)a), __builtin_amdgcn_readfirstlane((int)(a >> 32) & 0xffff),
                         __builtin_amdgcn_readfirstlane((int)bytes), 0x00027000};
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 ::"s"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(voff), "s"(rsrc)
+    asm volatile("s_nop 4\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                 ::"{m0}"(__builtin_amdgcn_readfirstlane((int)lds)), "v"(voff), "s"(rsrc)
                  : "memory");
 }
 
