@@ -905,7 +905,7 @@ int run_filter(const wv_model* m, int f, CView z, CView A, View out, int N, int 
 
 // One filter on one or two independent sets of N planes (a level's two column steps).  The three-layer
 // kernels take both sets in a launch: the coarse levels are a latency each, the fine ones fill their last
-// round better.  FP32 analysis of a 512 x 768 image in three planes: 1.05 ms, with two launches 1.17.
+// round better.  FP32 analysis of a 512 x 768 image in three planes: 1.02 ms, with two launches 1.18.
 int run_filters(const wv_model* m, bool split, int f, const LiftIO* io, int sets, int N, int h, int w, int predict,
                 float sign, float* a1, float* a2, hipStream_t s) {
     if (split) {

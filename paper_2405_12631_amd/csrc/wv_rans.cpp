@@ -67,7 +67,7 @@ struct TrimRow {
     }
 };
 
-// Trimmed tables (wv_cdf_trim): row i rebuilt from (lo, len) and its F values,
+// Trimmed tables (wv_cdf_trim): row i as (lo, len) and its F values (build: written out in full),
 // which start at offset off of packed; false if they do not describe a row.
 struct TrimRows {
     const uint8_t* lolen;
