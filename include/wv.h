@@ -63,7 +63,7 @@ typedef enum { WV_FP32 = 0, WV_BF16 = 1, WV_FP8 = 2 } wv_precision;
 /* Or-ed to the precision of wv_pack_bytes and wv_model_create: every synthesis
  * of the model (floats, bytes and impulse responses alike) takes its filters on
  * the 16-bit matrix units, each FP32 operand split into two or three 16-bit
- * parts (22 to 24 bits).  About 2.5 times as fast as FP32 with the same error
+ * parts (22 to 24 bits).  2 to 3.3 times as fast as FP32 with the same error
  * against 64 bits, but other last bits, and infinite subbands saturate the
  * filters where FP32 sums may give NaN.  Needs lift_ch 32, lift_layers 3,
  * lift_int 0 and filter weights of at most 2^24 (WV_EUNSUPPORTED otherwise).

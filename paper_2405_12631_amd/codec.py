@@ -84,7 +84,7 @@ class Model:
     """A model handle: weights uploaded and repacked on the current device.
 
     precision: WV_FP32, WV_BF16 or WV_FP8 context convs, `| WV_LIFT_SPLIT` for synthesis filters on
-    split 16-bit operands (about 2.5 times as fast, other last bits; see wv.h)."""
+    split 16-bit operands (2 to 3.3 times as fast, other last bits; see wv.h)."""
 
     def __init__(self, cfg, blob, precision=L.WV_FP32, device="cuda"):
         self.cfg = dict(cfg)
