@@ -24,20 +24,24 @@ inline uint32_t row_at(const uint16_t* row, int s, int nsym) {
 
 // The table of one coder step: its entry s, and the symbol of a slot (the largest s with
 // at(s) <= slot; at(0) = 0, at(nsym) = M).
+template <class Entry>
+int bisect(const Entry& entry, int nsym, uint32_t slot) {
+    int lo = 0, hi = nsym;   // invariant: entry(lo) <= slot < entry(hi), with entry(nsym) = M never read
+    while (hi - lo > 1) {
+        const int mid = (lo + hi) >> 1;
+        if (entry(mid) <= slot)
+            lo = mid;
+        else
+            hi = mid;
+    }
+    return lo;
+}
 struct FullRow {
     const uint16_t* row;
     int nsym;
     uint32_t at(int s) const { return row_at(row, s, nsym); }
     int find(uint32_t slot) const {
-        int lo = 0, hi = nsym;   // invariant: row[lo] <= slot < row_at(hi)
-        while (hi - lo > 1) {
-            const int mid = (lo + hi) >> 1;
-            if (row[mid] <= slot)
-                lo = mid;
-            else
-                hi = mid;
-        }
-        return lo;
+        return bisect([this](int s) { return row[s]; }, nsym, slot);
     }
 };
 // A trimmed row used as it is: outside the window an entry and a symbol are known from (lo, len)
@@ -66,6 +70,13 @@ struct TrimRow {
         return lo + k;
     }
 };
+// The same row searched as a full one.  In a row whose F falls somewhere (no wv_cdf_trim makes one) a slot
+// may lie in several symbols, and the two searches find different ones.
+struct TrimRowBisected : TrimRow {
+    int find(uint32_t slot) const {
+        return bisect([this](int s) { return at(s); }, nsym, slot);
+    }
+};
 
 // Trimmed tables (wv_cdf_trim): row i as (lo, len) and its F values (build: written out in full),
 // which start at offset off of packed; false if they do not describe a row.
@@ -77,7 +88,11 @@ struct TrimRows {
     bool row(long long i, long long off, TrimRow& r) const {
         const int lo = lolen[2 * i], len = lolen[2 * i + 1];
         if (lo < 1 || lo + len > nsym || off < 0 || off + len > count) return false;
-        r = TrimRow{packed + off, lo, len, nsym, (int)kM - nsym - 1};   // F_max - 1: the plateau above the window
+        r.f = packed + off;
+        r.lo = lo;
+        r.len = len;
+        r.nsym = nsym;
+        r.ftop = (int)kM - nsym - 1;   // F_max - 1: the plateau above the window
         return true;
     }
     bool build(long long i, long long off, uint16_t* tmp) const {
@@ -222,12 +237,19 @@ extern "C" int wv_rans_decode_trim(const uint8_t* lolen, const uint16_t* packed,
         (len > 0 && !in) || (packed_count > 0 && !packed))
         return WV_EINVAL;
     const TrimRows T{lolen, packed, packed_count, nsym};
-    long long off = 0;   // rows are visited first to last
-    return decode_rows<TrimRow>(
-        [&](long long i, TrimRow& r) {
-            const bool ok = T.row(i, off, r);
-            off += lolen[2 * i + 1];
-            return ok;
-        },
-        n, in, len, sym_out);
+    auto decode = [&](auto kind) {
+        using Row = decltype(kind);
+        long long off = 0;   // rows are visited first to last
+        return decode_rows<Row>(
+            [&](long long i, Row& r) {
+                const bool ok = T.row(i, off, r);
+                off += lolen[2 * i + 1];
+                return ok;
+            },
+            n, in, len, sym_out);
+    };
+    // A stream that fails is decoded again as the full tables would decode it, so that none is refused
+    // that wv_rans_decode takes.
+    const int rc = decode(TrimRow{});
+    return rc == WV_ECORRUPT ? decode(TrimRowBisected{}) : rc;
 }
